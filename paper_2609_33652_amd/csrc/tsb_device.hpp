@@ -127,6 +127,28 @@ __device__ __forceinline__ float load_logit(const void* base, size_t i) {
         return ((const float*)base)[i];
 }
 
+typedef unsigned short tsb_u16x2 __attribute__((ext_vector_type(2)));
+typedef short tsb_i16x2 __attribute__((ext_vector_type(2)));
+// Order-preserving signed 16-bit keys of the two bf16 patterns of a word
+// (a larger value has a larger key; -0 sits just below +0; NaN patterns sit
+// above +inf or below -inf by their sign).
+__device__ __forceinline__ tsb_i16x2 bf16_keys(uint32_t w) {
+    const tsb_i16x2 v = __builtin_bit_cast(tsb_i16x2, w);
+    const tsb_i16x2 sgn = v >> (tsb_i16x2){15, 15};  // 0 or -1 per half
+    return v ^ (sgn & (tsb_i16x2){0x7FFF, 0x7FFF});
+}
+
+// Key of the smallest bf16 value at least x (x not NaN): the pattern of a
+// positive x rounded up, of a negative x truncated toward zero.
+__device__ __forceinline__ int bf16_key_at_least(float x) {
+    const uint32_t b = __float_as_uint(x);
+    const uint32_t p = (b >> 31) ? (b >> 16) : ((b + 0xFFFFu) >> 16);
+    const int v = (int)(short)(uint16_t)p;
+    return v < 0 ? v ^ 0x7FFF : v;
+}
+
+constexpr int kBf16KeyMinusInf = -0x7F81;  // key of pattern 0xFF80
+
 // 16-byte load with the non-temporal hint, for data read exactly once.
 typedef unsigned int tsb_u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 load_stream16(const void* p) {
