@@ -93,16 +93,6 @@ __device__ __forceinline__ void load_batch(const void* target, size_t trow, int 
     }
 }
 
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t k) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint64_t ok = ((uint64_t)__shfl_xor((uint32_t)(k >> 32), o, kWave) << 32) |
-                            (uint32_t)__shfl_xor((uint32_t)k, o, kWave);
-        k = ok > k ? ok : k;
-    }
-    return k;
-}
-
 // Scores one batch. A group of four tokens whose largest logit, even with
 // the largest Gumbel value, stays below the wave's best key so far or below
 // the smallest key the largest logit of the batch can get, is skipped

@@ -184,29 +184,6 @@ __device__ __forceinline__ float wave_kth_largest_sorted(float x, int k) {
     return lane_f32(x, k - 1);
 }
 
-// One step of a wave maximum through DPP: lanes of the rows in ROWMASK take
-// the larger of their key and the key DPP control CTRL moves to them.
-template <int CTRL, int ROWMASK>
-__device__ __forceinline__ uint64_t dpp_max_step(uint64_t v) {
-    const int h = (int)(uint32_t)(v >> 32), l = (int)(uint32_t)v;
-    const uint32_t oh = (uint32_t)__builtin_amdgcn_update_dpp(h, h, CTRL, ROWMASK, 0xf, false);
-    const uint32_t ol = (uint32_t)__builtin_amdgcn_update_dpp(l, l, CTRL, ROWMASK, 0xf, false);
-    const uint64_t o = ((uint64_t)oh << 32) | ol;
-    return o > v ? o : v;
-}
-
-// Wave-uniform maximum of a uint64 key: within quads, half rows and rows by
-// DPP permutations, then row broadcasts carry the running maximum to lane 63.
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-    v = dpp_max_step<0xB1, 0xF>(v);   // quad_perm [1, 0, 3, 2]
-    v = dpp_max_step<0x4E, 0xF>(v);   // quad_perm [2, 3, 0, 1]
-    v = dpp_max_step<0x141, 0xF>(v);  // row_half_mirror
-    v = dpp_max_step<0x140, 0xF>(v);  // row_mirror
-    v = dpp_max_step<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
-    v = dpp_max_step<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
-    return lane_u64(v, kWave - 1);
-}
-
 // The K (<= 64) largest of the NR * 64 keys held NR per lane (0 = empty;
 // keys are distinct): lane r receives the r-th largest, lanes >= K and lanes
 // past the number of non-empty keys receive 0. Destroys v.

@@ -717,49 +717,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(VEC ? 7 
     C.flush(stats, lane);
 }
 
-// The walk's node record of u (a whole round: job.nrec set), from the same
-// loads and arithmetic as the walk would do. The parts that do not depend
-// on the children's tokens are read first (NodeHead), so their loads overlap
-// the merge; tok is child lane's token.
-struct NodeHead {
-    TreeNode t;
-    double L0, Ld;
-    int bad;
-};
-__device__ __forceinline__ NodeHead node_head(const TargetJob& job, const tsb_tree& tree, int r, int u, int n,
-                                              size_t tb, int D) {
-    NodeHead h;
-    h.t = tree_node(tree, tb, u, n, D);
-    h.L0 = 0.0;
-    h.bad = 0;
-    if (job.nrows > 0) h.L0 = target_row_lse(job.tm, job.ts, job.tf, job.P, tb + u, &h.bad);
-    h.Ld = (h.t.ok && h.t.m > 0) ? job.draft_lse[(size_t)r * D + h.t.d] : 0.0;
-    return h;
-}
-
-template <int DT>
-__device__ void write_record(const TargetJob& job, const NodeHead& h, const void* __restrict__ draft, int V, int D,
-                             float invT, int r, int u, size_t tb, int tok) {
-    const int lane = threadIdx.x;
-    const TreeNode& t = h.t;
-    uint32_t* rp = job.nrec + (tb + u) * kRecWords;
-    const int m = t.ok ? t.m : 0;
-    if (lane == 0) {
-        const uint64_t l0 = (uint64_t)__double_as_longlong(h.L0), ld = (uint64_t)__double_as_longlong(h.Ld);
-        *(uint4*)rp = make_uint4((uint32_t)m, (uint32_t)t.fc, (uint32_t)t.d,
-                                 (t.ok ? kRecOk : 0u) | (h.bad ? kRecTargetBad : 0u));
-        *(uint4*)(rp + 4) = make_uint4((uint32_t)l0, (uint32_t)(l0 >> 32), (uint32_t)ld, (uint32_t)(ld >> 32));
-    }
-    if (lane < m) {
-        const size_t trow = (tb + u) * (size_t)V;
-        const size_t drow = ((size_t)r * D + t.d) * (size_t)V;
-        const bool yok = tok >= 0 && tok < V;
-        const float xd = yok ? load_logit<DT>(draft, drow + tok) * invT : 0.f;
-        const float xt = yok ? load_logit<DT>(job.target, trow + tok) * invT : 0.f;
-        *(uint4*)(rp + 8 + 4 * lane) = make_uint4((uint32_t)tok, __float_as_uint(xd), __float_as_uint(xt), 0u);
-    }
-}
-
 template <int DT>
 __global__ __launch_bounds__(kWave) void replay_merge(int B, int D, int K, int T, tsb_tree tree,
                                                       const uint64_t* __restrict__ cand, const int* __restrict__ cc,
@@ -775,7 +732,13 @@ __global__ __launch_bounds__(kWave) void replay_merge(int B, int D, int K, int T
         if (lane == 0) node_tok[tb + u] = -1;
     }
     NodeHead head;
-    if (job.nrec && u < n) head = node_head(job, tree, r, u, n, tb, D);
+    if (job.nrec && u < n) {
+        head = node_head(tree, job.draft_lse, r, u, n, tb, D, lane);
+        if (job.nrows > 0) {
+            head.L0 = target_row_lse(job.tm, job.ts, job.tf, job.P, tb + u, &head.bad);
+            head.l0 = true;
+        }
+    }
     TreeNode nd;
     if (!replay_parent(tree, r, u, B, D, K, &nd)) {
         if (job.nrec && u < n) {
@@ -783,7 +746,7 @@ __global__ __launch_bounds__(kWave) void replay_merge(int B, int D, int K, int T
             // the tokens the caller's topology gave them
             const TreeNode& t = head.t;
             const int tok = (t.ok && lane < t.m) ? node_tok[tb + t.fc + lane] : -1;
-            write_record<DT>(job, head, draft, V, D, invT, r, u, tb, tok);
+            write_record<DT>(job.nrec, head, draft, job.target, V, D, invT, r, tb + u, tok, lane);
         }
         return;
     }
@@ -792,7 +755,7 @@ __global__ __launch_bounds__(kWave) void replay_merge(int B, int D, int K, int T
     // the children's tokens (lane j < m: child j), then the node record
     auto finish = [&](int tok) {
         if (lane < m) node_tok[tb + fc + lane] = tok;
-        if (job.nrec) write_record<DT>(job, head, draft, V, D, invT, r, u, tb, tok);
+        if (job.nrec) write_record<DT>(job.nrec, head, draft, job.target, V, D, invT, r, tb + u, tok, lane);
     };
     const size_t o = (tb + u) * (size_t)T;
     if (T <= kWave) {

@@ -39,8 +39,13 @@ __global__ __launch_bounds__(kBlock) void target_partials(const void* __restrict
                                                           long long chunk, int P, float invT,
                                                           const int32_t* __restrict__ n_nodes,
                                                           float* __restrict__ tm, double* __restrict__ ts,
-                                                          int* __restrict__ tf, XRegion X, int R) {
-    target_chunk<DT, VEC, kTargetPrefetch>(blockIdx.x, gridDim.x, target, V, B, nrows, chunk, P, invT, n_nodes, tm, ts, tf, X, R);
+                                                          int* __restrict__ tf, XRegion X, int R, int ngroups,
+                                                          RecordJob rec) {
+    if ((int)blockIdx.x >= ngroups) {
+        record_block<DT>(rec, (int)blockIdx.x - ngroups, invT);
+        return;
+    }
+    target_chunk<DT, VEC, kTargetPrefetch>(blockIdx.x, ngroups, target, V, B, nrows, chunk, P, invT, n_nodes, tm, ts, tf, X, R);
 }
 
 // ------------------------------------------------------------------ K5
@@ -64,7 +69,8 @@ struct WalkArgs {
     const int32_t* pool_tok;
     const float* trans;
     int P;
-    // node records (kRecWords per node) when the round's merge wrote them, else null
+    // node records (kRecWords per node), written by the round's merge or by the
+    // kernel before a walk launched on its own (not for the pool walk)
     const uint32_t* nrec;
     // the RRS walk reads each target row as it enters the node (else the row
     // normalisers come from a stream of every row, through the records or the
@@ -95,29 +101,24 @@ __device__ __forceinline__ SplitF split(double v) {
     return s;
 }
 
-// Block-wide binary64 sum (fixed order: lanes, then waves).
-__device__ double block_sum(double v) {
-    __shared__ double red[kBlock / kWave];
-    const double w = wave_sum(v);
-    if ((threadIdx.x % kWave) == 0) red[threadIdx.x / kWave] = w;
-    __syncthreads();
-    double tot = 0.0;
-    for (int i = 0; i < kBlock / kWave; ++i) tot += red[i];
-    __syncthreads();
-    return tot;
-}
-
 // ---------------------------------------------------------------- walk
-// A walk workgroup owns the slice [v0, v1) of the vocabulary. At every
-// visited node u with children, the first pass over the slice computes, in
-// binary64, p~_v = exp(a^t_{u,v} - L0) (L0 the streamed estimate of the
-// target normaliser) and q_v = exp(a^d_{depth(u),v} - lse_d), keeps both in
-// LDS and returns sum p~ (the exact normaliser is L0 + ln sum_v p~_v over the
-// request). The residual passes after rejections and the residual bonus then
-// read (p~, q) from LDS. Slices longer than the LDS cache are processed in
-// chunks that are recomputed in every pass.
-constexpr int kWalkThreads = 512;
-constexpr int kWalkCache = kWalkTokensPerGroup;  // tokens of (p~, q) held in LDS
+// A walk workgroup owns the slice [v0, v1) of the vocabulary; thread t owns
+// the slice's groups of four tokens at v0 + 4 (k kWalkThreads + t). The raw
+// logits of the node the walk is at are loaded into registers when it enters
+// the node; once the node needs them, every thread evaluates, in binary64,
+// p~_v = exp(a^t_{u,v} - L0) (L0 the streamed estimate of the target
+// normaliser) and q_v = exp(a^d_{depth(u),v} - lse_d) of its tokens into LDS,
+// where the residual passes after rejections and the residual bonus read them
+// (only the owner does: no barrier). Slices of up to kWalkSliceTokens leave
+// room for two workgroups on a compute unit; slices above kWalkHeldTokens are
+// recomputed in every pass.
+//
+// Bound by latency: a node is a chain of its record's load, its rows' load
+// and an exchange. Slices were 9728 tokens, one workgroup of 512 threads on a
+// compute unit with 19 tokens a thread to evaluate and to read in every pass.
+constexpr int kWalkThreads = kWalkThreadsPerGroup;
+constexpr int kWalkWaves = kWalkThreads / kWave;
+constexpr int kWalkPass = 4 * kWalkThreads;  // tokens of one group per thread
 
 template <int DT>
 __device__ __forceinline__ void load4_scaled(const void* base, size_t off, int valid, bool vec, float invT,
@@ -128,188 +129,277 @@ __device__ __forceinline__ void load4_scaled(const void* base, size_t off, int v
     for (int e = 0; e < 4; ++e) a[e] = e < valid ? x[e] * invT : -INFINITY;
 }
 
-// Block-wide binary64 sum for kWalkThreads threads (fixed order).
-__device__ double walk_sum(double v) {
-    __shared__ double red[kWalkThreads / kWave];
-    const double w = wave_sum(v);
-    if ((threadIdx.x % kWave) == 0) red[threadIdx.x / kWave] = w;
-    __syncthreads();
-    double tot = 0.0;
-    for (int i = 0; i < kWalkThreads / kWave; ++i) tot += red[i];
-    __syncthreads();
-    return tot;
-}
-
-// Four block-wide binary64 sums in one reduction (same fixed order as walk_sum).
-__device__ void walk_sum4(double (&v)[4]) {
-    __shared__ double red4[4][kWalkThreads / kWave];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = wave_sum(v[k]);
-    if ((threadIdx.x % kWave) == 0)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) red4[k][threadIdx.x / kWave] = v[k];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        double tot = 0.0;
-        for (int i = 0; i < kWalkThreads / kWave; ++i) tot += red4[k][i];
-        v[k] = tot;
-    }
-    __syncthreads();
-}
-
 struct WalkSlice {
-    int v0, v1, nchunks;
-    double* p;  // LDS [kWalkCache]
-    double* q;  // LDS [kWalkCache]
+    int v0, v1;
+    int groups;  // groups of four tokens in a whole slice
+    bool held;   // (p~, q) fit the LDS
 };
+__device__ __forceinline__ WalkSlice walk_slice(int V, int g, int G) {
+    // start a multiple of 4; an empty slice is [0, 0)
+    const int span = walk_span(V, G);
+    const bool has = (long long)g * span < V;
+    WalkSlice S;
+    S.v0 = has ? g * span : 0;
+    S.v1 = has ? min(V, S.v0 + span) : 0;
+    S.groups = span / 4;
+    S.held = span <= kWalkHeldTokens;  // the same for every workgroup of the request
+    return S;
+}
 
-// First pass at a node: fill (p~, q) for chunk c (into LDS when the slice has
-// one chunk) and return sum p~ over the chunk. Groups of four tokens per
-// thread; two groups are loaded before either is used.
+// The thread's index as a value the compiler takes for new each time: what a
+// pass derives from it (addresses, bounds, first random rounds) is recomputed
+// there instead of being kept in registers, or spilled, over the whole walk.
+__device__ __forceinline__ int pass_tid() {
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+// The thread's first kWalkRaw groups of one row as loaded; the logits of later
+// groups (slices above 4096 tokens have them) are read where they are used.
+constexpr int kWalkRaw = 2;
 template <int DT>
-__device__ double fill_chunk(const WalkArgs& A, bool vec, const WalkSlice& S, int c, size_t trow, size_t drow,
-                             double L0, double Ld, const double* et, bool store) {
-    const int c0 = S.v0 + c * kWalkCache;
-    const int n = min(kWalkCache, S.v1 - c0);
-    double acc = 0.0;
-    for (int base = 0; base * 4 < n; base += 2 * kWalkThreads) {
-        float at[2][4], ad[2][4];
+struct RawRow {
+    Raw4<DT> g[kWalkRaw];
+    __device__ __forceinline__ void load(const void* base, bool vec, const WalkSlice& S, size_t row) {
+        const int n = S.v1 - S.v0, tid = pass_tid();
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int i = (base + j * kWalkThreads + (int)threadIdx.x) * 4;
+        for (int k = 0; k < kWalkRaw; ++k) {
+            const int i = k * kWalkPass + tid * 4;
             const int valid = max(0, min(4, n - i));
-            load4_scaled<DT>(A.target, trow + c0 + (valid ? i : 0), valid, vec, A.invT, at[j]);
-            load4_scaled<DT>(A.draft, drow + c0 + (valid ? i : 0), valid, vec, A.invT, ad[j]);
+            raw_load4<DT>(base, row + S.v0 + (valid ? i : 0), valid, vec, g[k]);
         }
+    }
+};
+// Tokens of a thread's k-th group inside the slice (0 to 4).
+__device__ __forceinline__ int group_valid(const WalkSlice& S, int k, int tid) {
+    return max(0, min(4, S.v1 - S.v0 - k * kWalkPass - tid * 4));
+}
+// f(k, logits x scale of one row) for every group of the thread in the slice,
+// and f(k, target logits, draft logits). Compile-time k where the logits are
+// held (an index at run time would put them into scratch memory).
+template <int DT, typename F>
+__device__ __forceinline__ void row_groups(const void* base, bool vec, const WalkSlice& S, size_t row,
+                                           const RawRow<DT>& t, float scale, F f) {
+    const int tid = pass_tid();
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int i = (base + j * kWalkThreads + (int)threadIdx.x) * 4;
+    for (int k = 0; k < kWalkRaw; ++k) {
+        const int valid = group_valid(S, k, tid);
+        if (valid > 0) {
+            float a[4];
+            raw_scaled4<DT>(t.g[k], valid, scale, a);
+            f(k, tid, a);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll 1
+    for (int k = kWalkRaw; group_valid(S, k, tid) > 0; ++k) {
+        float a[4];
+        load4_scaled<DT>(base, row + S.v0 + k * kWalkPass + tid * 4, group_valid(S, k, tid), vec, scale, a);
+        f(k, tid, a);
+    }
+}
+template <int DT, typename F>
+__device__ __forceinline__ void row_pair_groups(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow,
+                                                size_t drow, const RawRow<DT>& t, const RawRow<DT>& d, F f) {
+    const int tid = pass_tid();
+#pragma unroll
+    for (int k = 0; k < kWalkRaw; ++k) {
+        const int valid = group_valid(S, k, tid);
+        if (valid > 0) {
+            float at[4], ad[4];
+            raw_scaled4<DT>(t.g[k], valid, A.invT, at);
+            raw_scaled4<DT>(d.g[k], valid, A.invT, ad);
+            f(k, tid, at, ad);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll 1
+    for (int k = kWalkRaw; group_valid(S, k, tid) > 0; ++k) {
+        float at[4], ad[4];
+        const size_t o = S.v0 + (size_t)k * kWalkPass + tid * 4;
+        load4_scaled<DT>(A.target, trow + o, group_valid(S, k, tid), vec, A.invT, at);
+        load4_scaled<DT>(A.draft, drow + o, group_valid(S, k, tid), vec, A.invT, ad);
+        f(k, tid, at, ad);
+    }
+}
+// Groups of this thread in the slice.
+__device__ __forceinline__ int slice_groups(const WalkSlice& S, int tid) {
+    return max(0, (S.v1 - S.v0 - tid * 4 + kWalkPass - 1) / kWalkPass);
+}
+
+__device__ __forceinline__ double exp_or_0(float a, double L, const double* et) {
+    return a > -INFINITY ? exp64((double)a - L, et) : 0.0;
+}
+
+// (p~, q) of the thread's tokens in LDS (0 past the slice): token e of group
+// i at e * groups + i, so that a wave's accesses are to consecutive words.
+struct HeldPQ {
+    double* lds;
+    int groups;
+    __device__ __forceinline__ double& p(int k, int e, int tid) const { return lds[e * groups + k * kWalkThreads + tid]; }
+    __device__ __forceinline__ double& q(int k, int e, int tid) const {
+        return lds[(4 + e) * groups + k * kWalkThreads + tid];
+    }
+    // Evaluates them, calling f(p~, q) for each token.
+    template <int DT, typename F>
+    __device__ __forceinline__ void fill(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow, size_t drow,
+                                         const RawRow<DT>& t, const RawRow<DT>& d, double L0, double Ld,
+                                         const double* et, F f) const {
+        row_pair_groups<DT>(A, vec, S, trow, drow, t, d, [&](int k, int tid, const float(&at)[4], const float(&ad)[4]) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (i + e >= n) break;
-                const double pt = at[j][e] > -INFINITY ? exp64((double)at[j][e] - L0, et) : 0.0;
-                const double qd = ad[j][e] > -INFINITY ? exp64((double)ad[j][e] - Ld, et) : 0.0;
-                acc += pt;
-                if (store) {
-                    S.p[i + e] = pt;
-                    S.q[i + e] = qd;
-                }
+                const double pt = exp_or_0(at[e], L0, et), qd = exp_or_0(ad[e], Ld, et);
+                p(k, e, tid) = pt;
+                q(k, e, tid) = qd;
+                if (e & 1) __builtin_amdgcn_sched_barrier(0);  // four exponentials in flight
+                f(pt, qd);
             }
-        }
+        });
     }
-    return acc;
-}
+    // sum over the thread's tokens of max(a p~ - c q, 0)
+    __device__ __forceinline__ double residual(const WalkSlice& S, double a, double c) const {
+        const int tid = pass_tid(), ng = slice_groups(S, tid);
+        double z = 0.0;
+#pragma unroll 1
+        for (int k = 0; k < ng; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double rr = p(k, e, tid) * a - c * q(k, e, tid);
+                z += rr > 0.0 ? rr : 0.0;
+            }
+        return z;
+    }
+};
 
-// Token-wise visit of (p = p~ * inv, q) over the slice: from LDS when cached,
-// else recomputed chunk by chunk. f(token, p, q) is called for every token.
+// Token-wise visit of (p~, q) over a slice that is not held, recomputed:
+// f(token, p~, q).
 template <int DT, typename F>
-__device__ void visit_pq(const WalkArgs& A, bool vec, const WalkSlice& S, bool cached, size_t trow, size_t drow,
-                         double L0, double inv, double Ld, const double* et, F f) {
-    if (cached) {
-        const int n = S.v1 - S.v0;
-        for (int i = threadIdx.x; i < n; i += kWalkThreads) f(S.v0 + i, S.p[i] * inv, S.q[i]);
-        return;
-    }
-    for (int c = 0; c < S.nchunks; ++c) {
-        const int c0 = S.v0 + c * kWalkCache;
-        const int n = min(kWalkCache, S.v1 - c0);
-        for (int i4 = threadIdx.x; i4 * 4 < n; i4 += kWalkThreads) {
-            const int i = i4 * 4;
-            const int valid = min(4, n - i);
-            float at[4], ad[4];
-            load4_scaled<DT>(A.target, trow + c0 + i, valid, vec, A.invT, at);
-            load4_scaled<DT>(A.draft, drow + c0 + i, valid, vec, A.invT, ad);
-            for (int e = 0; e < valid; ++e) {
-                const double pt = at[e] > -INFINITY ? exp64((double)at[e] - L0, et) : 0.0;
-                const double qd = ad[e] > -INFINITY ? exp64((double)ad[e] - Ld, et) : 0.0;
-                f(c0 + i + e, pt * inv, qd);
-            }
-        }
-    }
-}
-
-// (key, token) argmax across the workgroup: key desc, token asc.
-__device__ void walk_argmax(float* best, int* bidx) {
-    float b = *best;
-    int bi = *bidx;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const float ok = __shfl_xor(b, off, kWave);
-        const int oi = __shfl_xor(bi, off, kWave);
-        if (ok > b || (ok == b && oi < bi)) {
-            b = ok;
-            bi = oi;
-        }
-    }
-    __shared__ float rk[kWalkThreads / kWave];
-    __shared__ int ri[kWalkThreads / kWave];
-    if ((threadIdx.x % kWave) == 0) {
-        rk[threadIdx.x / kWave] = b;
-        ri[threadIdx.x / kWave] = bi;
-    }
-    __syncthreads();
-    b = rk[0];
-    bi = ri[0];
-    for (int i = 1; i < kWalkThreads / kWave; ++i)
-        if (rk[i] > b || (rk[i] == b && ri[i] < bi)) {
-            b = rk[i];
-            bi = ri[i];
-        }
-    __syncthreads();
-    *best = b;
-    *bidx = bi;
-}
-
-// Bonus sample from p_u alone (leaf, or empty residual): argmax ln p_v + G_v,
-// read straight from the target row.
-template <int DT>
-__device__ void bonus_from_p(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow, double Lt,
-                             const RngKey& key, uint32_t node, float* bk, int* bi) {
-    float best = -INFINITY;
-    int bidx = 0x7FFFFFFF;
-    const SplitF Ls = split(Lt);
+__device__ __forceinline__ void visit_pq(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow, size_t drow,
+                                         double L0, double Ld, const double* et, F f) {
     const int n = S.v1 - S.v0;
-    // two groups of four per thread and iteration, both loads issued before
-    // either is used
-    for (int i4 = threadIdx.x; i4 * 4 < n; i4 += 2 * kWalkThreads) {
-        float at[2][4];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int i = (i4 + h * kWalkThreads) * 4;
-            const int valid = max(0, min(4, n - i));
-            load4_scaled<DT>(A.target, trow + S.v0 + (valid ? i : 0), valid, vec, A.invT, at[h]);
+    for (int i = pass_tid() * 4; i < n; i += kWalkPass) {
+        const int valid = min(4, n - i);
+        float at[4], ad[4];
+        load4_scaled<DT>(A.target, trow + S.v0 + i, valid, vec, A.invT, at);
+        load4_scaled<DT>(A.draft, drow + S.v0 + i, valid, vec, A.invT, ad);
+        for (int e = 0; e < valid; ++e) f(S.v0 + i + e, exp_or_0(at[e], L0, et), exp_or_0(ad[e], Ld, et));
+    }
+}
+
+// A Gumbel-max candidate of the thread: largest key, its smallest token.
+struct BestKey {
+    float k = -INFINITY;
+    int v = 0x7FFFFFFF;
+    __device__ __forceinline__ void offer(float key, int tok) {
+        if (key > k || (key == k && tok < v)) {
+            k = key;
+            v = tok;
         }
+    }
+    // as one ordered word: key descending, then token ascending
+    __device__ __forceinline__ uint64_t packed() const {
+        return ((uint64_t)ordered_bits(k) << 32) | (uint32_t)~v;
+    }
+};
+
+// Bonus sample from p_u alone (leaf, or empty residual): argmax ln p_v + G_v
+// over the slice.
+template <int DT>
+__device__ __forceinline__ BestKey bonus_from_p(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow,
+                                                const RawRow<DT>& t, double Lt, const RngKey& key, uint32_t node) {
+    BestKey b;
+    const SplitF Ls = split(Lt);
+    row_groups<DT>(A.target, vec, S, trow, t, A.invT, [&](int k, int tid, const float(&at)[4]) {
+        const int v = S.v0 + k * kWalkPass + tid * 4;
+        const uint4 w = rng_block(key, node, kStreamBonus, (uint32_t)(v >> 2));
+        const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int i = (i4 + h * kWalkThreads) * 4;
-            const int valid = max(0, min(4, n - i));
-            if (valid == 0) continue;
-            const uint4 w = rng_block(key, node, kStreamBonus, (uint32_t)((S.v0 + i) >> 2));
+        for (int e = 0; e < 4; ++e)
+            if (at[e] > -INFINITY) b.offer(((at[e] - Ls.hi) - Ls.lo) + gumbel_f32(ws[e]), v + e);
+    });
+    return b;
+}
+
+// Gumbel-max of ln max(a p~ - c q, 0) over the slice, and the thread's part of
+// the residual's mass.
+template <int DT>
+__device__ __forceinline__ BestKey bonus_residual(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow,
+                                                  size_t drow, const HeldPQ& pq, double L0, double Ld, double a,
+                                                  double c, const double* et, const RngKey& key, uint32_t node,
+                                                  double& mass) {
+    BestKey b;
+    mass = 0.0;
+    if (S.held) {
+        const int tid = pass_tid(), ng = slice_groups(S, tid);
+#pragma unroll 1
+        for (int k = 0; k < ng; ++k) {
+            const int v = S.v0 + k * kWalkPass + tid * 4;
+            const uint4 w = rng_block(key, node, kStreamBonus, (uint32_t)(v >> 2));
             const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (e >= valid || at[h][e] == -INFINITY) continue;
-                const float kv = ((at[h][e] - Ls.hi) - Ls.lo) + gumbel_f32(ws[e]);  // ln p_v + G_v
-                const int v = S.v0 + i + e;
-                if (kv > best || (kv == best && v < bidx)) {
-                    best = kv;
-                    bidx = v;
+                const double rr = pq.p(k, e, tid) * a - c * pq.q(k, e, tid);
+                if (rr > 0.0) {
+                    mass += rr;
+                    b.offer(logf((float)rr) + gumbel_f32(ws[e]), v + e);
                 }
             }
         }
+    } else {
+        visit_pq<DT>(A, vec, S, trow, drow, L0, Ld, et, [&](int v, double p, double q) {
+            const double rr = p * a - c * q;
+            if (rr > 0.0) {
+                mass += rr;
+                b.offer(logf((float)rr) + gumbel_f32(rng_word(key, node, kStreamBonus, (uint32_t)v)), v);
+            }
+        });
     }
-    walk_argmax(&best, &bidx);
-    *bk = best;
-    *bi = bidx;
+    return b;
 }
 
-// Exchange among the G workgroups of a request through the request's
-// tagged slots: each contributes up to four binary64 partials (and
-// optionally a (key, token) pair); everyone gets the sums (a fixed reduction
-// tree over the workgroups, so every run adds in the same order) and the
-// best pair. Partials travel with 2^-44 relative resolution.
+// Block reductions and exchanges among the G workgroups of a request in one:
+// the waves' parts meet in LDS, wave 0 adds them, publishes up to four words
+// into the workgroup's slot (one lane a word, one store instruction), polls
+// the slots of all G workgroups (lane l: word l % 4 of slot l / 4 and of every
+// 16th slot after it, the loads of four such sets in flight together) and
+// hands the result back through LDS: two barriers a round, the LDS buffers
+// double-buffered by the round's parity. Everyone gets the same bits: sums are
+// added in a fixed order. Partials travel with 2^-44 relative resolution.
+// Among 16 workgroups a round takes 1.3 us (1.9 with a thread storing all
+// words and a lane loading each slot's words in turn), among 38 about 1.7.
+// One workgroup alone exchanges nothing.
 constexpr int kExVals = 4;
+constexpr int kExSets = 4;                       // slot sets in flight
+constexpr int kExPer = kWave / kExVals;          // slots a set covers
+
+// Wave sum through DPP row shifts and broadcasts; the total is in lane 63.
+template <int CTRL, int ROWMASK>
+__device__ __forceinline__ double dpp_add_step(double v) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWMASK, 0xf, true);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWMASK, 0xf, true);
+    return v + __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_sum_last(double v) {
+    v = dpp_add_step<0x111, 0xF>(v);  // row_shr:1
+    v = dpp_add_step<0x112, 0xF>(v);  // row_shr:2
+    v = dpp_add_step<0x114, 0xF>(v);  // row_shr:4
+    v = dpp_add_step<0x118, 0xF>(v);  // row_shr:8
+    v = dpp_add_step<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_add_step<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+__device__ __forceinline__ double xor_f64(double v, int j) {
+    return __longlong_as_double((long long)shfl_xor_u64((uint64_t)__double_as_longlong(v), j));
+}
+// the value of lane Q of the lane's quad
+template <int Q>
+__device__ __forceinline__ uint64_t quad_u64(uint64_t v) {
+    constexpr int c = Q * 0x55;
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), c, 0xF, 0xF, true);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, c, 0xF, 0xF, true);
+    return ((uint64_t)hi << 32) | lo;
+}
 
 struct Exchange {
     const WalkArgs* A;
@@ -317,252 +407,266 @@ struct Exchange {
     uint32_t nb;  // rounds run
     int timeout;
 
-    template <int NV, bool BEST>
-    __device__ void run(const double (&part)[NV], double (&tot)[NV], float bk, int bi, float* fk, int* fi) {
-        static_assert(NV <= kExVals, "exchange width");
-        constexpr int NW = NV + (BEST ? 2 : 0);
-        uint64_t w[NW];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) w[i] = xpack_f64(part[i]);
-        if (BEST) {
-            w[NV] = xpack_u32(ordered_bits(bk));
-            w[NW - 1] = xpack_u32((uint32_t)bi);
+    // Wave 0: lanes 0 to 3 publish their word, then f(set base, q) gets the
+    // words of 64 slots at a time: q[c] holds word lane % 4 of slot
+    // base + 16 c + lane / 4 (0 past G). Returns whether a wait was abandoned.
+    template <typename F>
+    __device__ __forceinline__ int round(uint64_t mine, F f) {
+        const int lane = threadIdx.x;
+        if (G == 1) {
+            uint64_t q[kExSets] = {lane < kExVals ? mine & ~kTagMask : 0ull, 0ull, 0ull, 0ull};
+            f(0, q);
+            return 0;
         }
-        xpublish<NW>(A->X, r, g, nb, w);
-        // wave 0 polls the G slots (lane h: slots h and h + 64), reduces them
-        // in a fixed order and hands the result to the others
-        __shared__ double s_tot[kExVals];
-        __shared__ float s_bk;
-        __shared__ int s_bi, s_to;
-        if (threadIdx.x < kWave) {
-            const int lane = threadIdx.x;
-            double v[NV];
-            uint32_t kb = 0u, ib = 0xFFFFFFFFu;
-            int to = 0;
+        const uint64_t t = xtag(nb);
+        uint64_t* const s = xslot(A->X, r, nb, 0);
+        if (lane < kExVals)
+            __hip_atomic_store(&s[(size_t)g * kSlotWords + lane], (mine & ~kTagMask) | t, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        int to = 0;
+        for (int b = 0; b < G; b += kExSets * kExPer) {
+            uint64_t q[kExSets];
+            for (uint32_t spins = 0;; ++spins) {
+                bool ok = true;
 #pragma unroll
-            for (int i = 0; i < NV; ++i) v[i] = 0.0;
+                for (int c = 0; c < kExSets; ++c) {
+                    const int h = b + c * kExPer + lane / kExVals;
+                    q[c] = t;
+                    if (h < G)
+                        q[c] = __hip_atomic_load(&s[(size_t)h * kSlotWords + lane % kExVals], __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+                }
 #pragma unroll
-            for (int half = 0; half < kWalkGroupsMax / kWave; ++half) {
-                const int h = lane + half * kWave;
-                if (h < G) {
-                    uint64_t q[NW];
-                    if (!xpoll<NW>(A->X, r, h, nb, q)) to = 1;
-#pragma unroll
-                    for (int i = 0; i < NV; ++i) v[i] += xunpack_f64(q[i]);
-                    if (BEST) {
-                        const uint32_t k = xunpack_u32(q[NV]), ix = xunpack_u32(q[NW - 1]);
-                        if (k > kb || (k == kb && ix < ib)) {
-                            kb = k;
-                            ib = ix;
-                        }
-                    }
+                for (int c = 0; c < kExSets; ++c) ok = ok && (q[c] & kTagMask) == t;
+                if (__ballot(!ok) == 0ull) break;
+                if (spins >= kPollLimit) {
+                    to = 1;
+                    break;
                 }
             }
 #pragma unroll
-            for (int i = 0; i < NV; ++i) v[i] = wave_sum(v[i]);
-            if (BEST) {
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) {
-                    const uint32_t ok = (uint32_t)__shfl_xor((int)kb, off, kWave);
-                    const uint32_t oi = (uint32_t)__shfl_xor((int)ib, off, kWave);
-                    if (ok > kb || (ok == kb && oi < ib)) {
-                        kb = ok;
-                        ib = oi;
-                    }
-                }
-            }
-            to = wave_or(to);
-            if (lane == 0) {
-#pragma unroll
-                for (int i = 0; i < NV; ++i) s_tot[i] = v[i];
-                s_bk = kb ? from_ordered_bits(kb) : -INFINITY;
-                s_bi = (int)ib;
-                s_to = to;
-            }
+            for (int c = 0; c < kExSets; ++c) q[c] = b + c * kExPer + lane / kExVals < G ? q[c] & ~kTagMask : 0ull;
+            f(b, q);
         }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < NV; ++i) tot[i] = s_tot[i];
-        if (BEST) {
-            *fk = s_bk;
-            *fi = s_bi;
-        }
-        if (s_to) timeout = 1;
-        ++nb;
-        __syncthreads();  // s_tot is rewritten by the next exchange
+        return to;
     }
+
+    // v[k]: the thread's parts in, the request's sums out.
     template <int NV>
-    __device__ void run(const double (&part)[NV], double (&tot)[NV]) {
-        run<NV, false>(part, tot, 0.f, 0, nullptr, nullptr);
-    }
-    __device__ double sum(double part) {
-        double p[1] = {part}, t[1];
-        run<1>(p, t);
-        return t[0];
-    }
-    __device__ int best(float bk, int bi, double part, double* tot) {
-        double p[1] = {part}, t[1];
-        float fk;
-        int fi;
-        run<1, true>(p, t, bk, bi, &fk, &fi);
-        *tot = t[0];
-        return fk > -INFINITY ? fi : -1;
-    }
-    // Log-sum-exp of the workgroups' (max a, sum exp(a - max a)) pairs: the
-    // largest max, then every sum rescaled to it and added in a fixed order
-    // (every workgroup gets the same value). *bad if a workgroup flagged its
-    // part, or if no part holds a finite logit.
-    __device__ double lse(double mx, double s, bool part_bad, bool* bad) {
-        constexpr int NH = kWalkGroupsMax / kWave;
-        const uint64_t w[3] = {xpack_f64(mx), xpack_f64(s), xpack_u32(part_bad ? 1u : 0u)};
-        xpublish<3>(A->X, r, g, nb, w);
-        __shared__ double s_l;
-        __shared__ int s_b, s_to;
-        if (threadIdx.x < kWave) {
-            const int lane = threadIdx.x;
-            double hm[NH], hs[NH];
-            int b = 0, to = 0;
-            double M = -INFINITY;
+    __device__ __forceinline__ void sum(double (&v)[NV]) {
+        static_assert(NV <= kExVals && kWalkWaves * kExVals <= kWave, "exchange width");
+        __shared__ double s_red[2][kExVals][kWalkWaves];
+        __shared__ double s_tot[2][kExVals];
+        __shared__ int s_to[2];
+        const int par = (int)(nb & 1u), lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
 #pragma unroll
-            for (int half = 0; half < NH; ++half) {
-                const int h = lane + half * kWave;
-                hm[half] = -INFINITY;
-                hs[half] = 0.0;
-                if (h < G) {
-                    uint64_t q[3];
-                    if (!xpoll<3>(A->X, r, h, nb, q)) to = 1;
-                    hm[half] = xunpack_f64(q[0]);
-                    hs[half] = xunpack_f64(q[1]);
-                    b |= xunpack_u32(q[2]) != 0u;
-                }
-                M = fmax(M, hm[half]);
+        for (int k = 0; k < NV; ++k) v[k] = wave_sum_last(v[k]);
+        if (lane == kWave - 1)
+#pragma unroll
+            for (int k = 0; k < NV; ++k) s_red[par][k][wave] = v[k];
+        __syncthreads();
+        if (wave == 0) {
+            double x = lane < NV * kWalkWaves ? s_red[par][lane / kWalkWaves][lane % kWalkWaves] : 0.0;
+#pragma unroll
+            for (int j = 1; j < kWalkWaves; j <<= 1) x += xor_f64(x, j);
+            const double mine = __shfl(x, (lane % kExVals) * kWalkWaves, kWave);
+            double tot = 0.0;
+            const int to = round((uint64_t)__double_as_longlong(mine), [&](int, const uint64_t(&q)[kExSets]) {
+#pragma unroll
+                for (int c = 0; c < kExSets; ++c) tot += __longlong_as_double((long long)q[c]);
+            });
+#pragma unroll
+            for (int j = kExVals; j < kWave; j <<= 1) tot += xor_f64(tot, j);
+            if (lane < kExVals) s_tot[par][lane] = tot;
+            if (lane == 0) s_to[par] = to;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NV; ++k) v[k] = s_tot[par][k];
+        if (s_to[par]) timeout = 1;
+        ++nb;
+    }
+
+    // The request's best key's token (-1: none), and the sum of `part`.
+    __device__ __forceinline__ int best(const BestKey& b, double part, double* total) {
+        __shared__ uint64_t s_key[2][kWalkWaves];
+        __shared__ double s_red[2][kWalkWaves];
+        __shared__ double s_tot[2];
+        __shared__ uint64_t s_best[2];
+        __shared__ int s_to[2];
+        const int par = (int)(nb & 1u), lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+        const uint64_t wk = wave_max_u64(b.packed());
+        const double ws = wave_sum_last(part);
+        if (lane == kWave - 1) {
+            s_key[par][wave] = wk;
+            s_red[par][wave] = ws;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            uint64_t k = lane < kWalkWaves ? s_key[par][lane] : 0ull;
+            double x = lane < kWalkWaves ? s_red[par][lane] : 0.0;
+#pragma unroll
+            for (int j = 1; j < kWalkWaves; j <<= 1) {
+                const uint64_t o = shfl_xor_u64(k, j);
+                k = o > k ? o : k;
+                x += xor_f64(x, j);
             }
+            k = lane_u64(k, 0);
+            x = lane_f64(x, 0);
+            // words: mass, key, token
+            const uint64_t mine = lane == 0 ? (uint64_t)__double_as_longlong(x)
+                                            : (lane == 1 ? (k >> 32) << 32 : (lane == 2 ? k << 32 : 0ull));
+            uint64_t top = 0ull;
+            double tot = 0.0;
+            const int to = round(mine, [&](int, const uint64_t(&q)[kExSets]) {
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) M = fmax(M, __shfl_xor(M, off, kWave));
-            double t = 0.0;
-            if (M > -INFINITY)
+                for (int c = 0; c < kExSets; ++c) {
+                    const uint64_t kk = quad_u64<1>(q[c]) | (quad_u64<2>(q[c]) >> 32);
+                    top = kk > top ? kk : top;
+                    tot += __longlong_as_double((long long)quad_u64<0>(q[c]));
+                }
+            });
 #pragma unroll
-                for (int half = 0; half < NH; ++half)
-                    if (hm[half] > -INFINITY) t += hs[half] * exp(hm[half] - M);
-            t = wave_sum(t);
-            b = wave_or(b);
-            to = wave_or(to);
+            for (int j = kExVals; j < kWave; j <<= 1) {
+                const uint64_t o = shfl_xor_u64(top, j);
+                top = o > top ? o : top;
+                tot += xor_f64(tot, j);
+            }
             if (lane == 0) {
-                const bool none = !(M > -INFINITY) || !(t > 0.0);
-                s_l = none ? 0.0 : M + log(t);
-                s_b = b || none || !isfinite(M) || !isfinite(t);
-                s_to = to;
+                s_tot[par] = tot;
+                s_best[par] = top;
+                s_to[par] = to;
             }
         }
         __syncthreads();
-        const double L = s_l;
-        *bad = s_b != 0;
-        if (s_to) timeout = 1;
+        *total = s_tot[par];
+        const uint64_t top = s_best[par];
+        if (s_to[par]) timeout = 1;
         ++nb;
-        __syncthreads();  // s_l is rewritten by the next exchange
+        // a key of -inf is no candidate
+        return (uint32_t)(top >> 32) > ordered_bits(-INFINITY) ? (int)~(uint32_t)top : -1;
+    }
+
+    // Log-sum-exp of the request's row from the threads' parts (m the largest
+    // raw logit, s = sum 2^((x - m) c), c = invT log2(e); nf: a NaN or +inf):
+    // the largest maximum, then every sum rescaled to it and added in a fixed
+    // order. *bad if a part is unusable, or if none holds a finite logit.
+    __device__ __forceinline__ double lse(float m, double s, bool nf, float c, float invT, const double* s_exp,
+                                          bool* bad) {
+        __shared__ float s_m[2][kWalkWaves];
+        __shared__ double s_s[2][kWalkWaves];
+        __shared__ int s_nf[2][kWalkWaves];
+        __shared__ double s_l[2];
+        __shared__ int s_b[2], s_to[2];
+        const int par = (int)(nb & 1u), lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+        const float wm = wave_max(m);
+        const double ws = wave_sum_last(m == -INFINITY ? 0.0 : (m == wm ? s : s * (double)exp2f((m - wm) * c)));
+        const bool wnf = __ballot(nf) != 0ull;
+        if (lane == kWave - 1) {
+            s_m[par][wave] = wm;
+            s_s[par][wave] = ws;
+            s_nf[par][wave] = wnf ? 1 : 0;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            float M = -INFINITY;
+            bool pb = false;
+            for (int w = 0; w < kWalkWaves; ++w) {
+                M = fmaxf(M, s_m[par][w]);
+                pb = pb || s_nf[par][w] != 0;
+            }
+            double x = 0.0;
+            if (lane < kWalkWaves && M > -INFINITY && M < INFINITY && s_m[par][lane] > -INFINITY)
+                x = s_s[par][lane] * (double)exp2f((s_m[par][lane] - M) * c);
+#pragma unroll
+            for (int j = 1; j < kWalkWaves; j <<= 1) x += xor_f64(x, j);
+            x = lane_f64(x, 0);
+            pb = pb || M == INFINITY || !isfinite(x);
+            const double mx = M > -INFINITY && !pb ? (double)(M * invT) : -INFINITY;
+            const double sx = pb ? 0.0 : x;
+            // words: maximum, sum, flag
+            const uint64_t mine = lane == 0 ? (uint64_t)__double_as_longlong(mx)
+                                            : (lane == 1 ? (uint64_t)__double_as_longlong(sx)
+                                                         : (lane == 2 ? xpack_u32(pb ? 1u : 0u) : 0ull));
+            double T = 0.0, top = -INFINITY;  // running sum and its reference
+            int b = 0;
+            const int to = round(mine, [&](int base, const uint64_t(&q)[kExSets]) {
+                double hm[kExSets], M2 = top;
+#pragma unroll
+                for (int c4 = 0; c4 < kExSets; ++c4) {
+                    hm[c4] = base + c4 * kExPer + lane / kExVals < G
+                                 ? __longlong_as_double((long long)quad_u64<0>(q[c4]))
+                                 : -INFINITY;
+                    b |= quad_u64<2>(q[c4]) != 0ull ? 1 : 0;
+                    M2 = fmax(M2, hm[c4]);
+                }
+#pragma unroll
+                for (int j = kExVals; j < kWave; j <<= 1) M2 = fmax(M2, xor_f64(M2, j));
+                double t = 0.0;
+#pragma unroll
+                for (int c4 = 0; c4 < kExSets; ++c4)
+                    if (hm[c4] > -INFINITY)
+                        t += __longlong_as_double((long long)quad_u64<1>(q[c4])) * exp64x(hm[c4] - M2, s_exp);
+#pragma unroll
+                for (int j = kExVals; j < kWave; j <<= 1) t += xor_f64(t, j);
+                T = (top > -INFINITY ? T * exp64x(top - M2, s_exp) : 0.0) + t;
+                top = M2;
+            });
+            const bool anyb = __ballot(b) != 0ull;
+            if (lane == 0) {
+                const bool none = !(top > -INFINITY) || !(T > 0.0);
+                s_l[par] = none ? 0.0 : top + log64(T, s_exp);
+                s_b[par] = anyb || none || !isfinite(top) || !isfinite(T);
+                s_to[par] = to;
+            }
+        }
+        __syncthreads();
+        const double L = s_l[par];
+        *bad = s_b[par] != 0;
+        if (s_to[par]) timeout = 1;
+        ++nb;
         return L;
     }
 };
 
 // Streamed normaliser of the target row of the node the walk enters (the
-// walk reads a target row only when it enters its node): each workgroup
-// streams its slice (running maximum m of the raw logits, binary32 terms
-// 2^(x c - m c) with c = invT log2(e), added in binary64, as the target
-// stream does), then the request's workgroups combine their parts by one
-// exchange. Within ~1e-6 of ln sum_v exp(a_v); *bad if the row holds a NaN
-// or +inf logit, or no finite one. The slice is read in batches of
-// kRowGroups groups of four logits per thread (one batch covers a slice of
-// up to 10240 logits).
-constexpr int kRowGroups = 5;
-template <int DT>
-struct RowBatch {
-    Raw4<DT> g[kRowGroups];
-};
-
-template <int DT>
-__device__ __forceinline__ void row_batch_load(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow, int base,
-                                               RowBatch<DT>& rb) {
-    const int n = S.v1 - S.v0;
-#pragma unroll
-    for (int k = 0; k < kRowGroups; ++k) {
-        const int i = base + (k * kWalkThreads + (int)threadIdx.x) * 4;
-        const int valid = max(0, min(4, n - i));
-        raw_load4<DT>(A.target, trow + S.v0 + (valid ? i : 0), valid, vec, rb.g[k]);
-    }
-}
-
-template <int DT>
-__device__ double entered_row_lse(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow, Exchange& X,
-                                  bool* bad) {
-    const float c = A.invT * 1.4426950408889634f;
-    const int n = S.v1 - S.v0;
-    constexpr int kBatch = kRowGroups * 4 * kWalkThreads;
+// walk reads a target row only when it enters its node): every thread's
+// running maximum of the raw logits and binary32 terms 2^(x c - m c) added in
+// binary64, as the target stream does, then one exchange. Within ~1e-6 of ln
+// sum_v exp(a_v); *bad if the row holds a NaN or +inf logit, or no finite one.
+struct RowPart {
     float m = -INFINITY;
     double sum = 0.0;
     bool nf = false;
-    for (int base = 0; base < n; base += kBatch) {
-        RowBatch<DT> rb;
-        row_batch_load<DT>(A, vec, S, trow, base, rb);
-        float x[kRowGroups][4];
-#pragma unroll
-        for (int k = 0; k < kRowGroups; ++k) {
-            if (DT == TSB_BF16) {
-                x[k][0] = __uint_as_float(rb.g[k].w[0] << 16);
-                x[k][1] = __uint_as_float(rb.g[k].w[0] & 0xFFFF0000u);
-                x[k][2] = __uint_as_float(rb.g[k].w[1] << 16);
-                x[k][3] = __uint_as_float(rb.g[k].w[1] & 0xFFFF0000u);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[k][e] = __uint_as_float(rb.g[k].w[e]);
-            }
-        }
+    __device__ __forceinline__ void add(const float (&x)[4], float c) {
         float cm = m;
 #pragma unroll
-        for (int k = 0; k < kRowGroups; ++k)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                nf |= __builtin_amdgcn_classf(x[k][e], 0x203);  // signalling NaN, quiet NaN, +inf
-                cm = fmaxf(cm, x[k][e]);                        // NaN is ignored
-            }
+        for (int e = 0; e < 4; ++e) {
+            nf |= __builtin_amdgcn_classf(x[e], 0x203);  // signalling NaN, quiet NaN, +inf
+            cm = fmaxf(cm, x[e]);                        // NaN is ignored
+        }
         if (cm > m) {
             if (m > -INFINITY) sum *= (double)exp2f((m - cm) * c);
             m = cm;
         }
         if (m > -INFINITY && m < INFINITY) {
             const float mc = m * c;
+            float cs = 0.f;
 #pragma unroll
-            for (int k = 0; k < kRowGroups; ++k) {
-                float cs = 0.f;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) cs += __builtin_amdgcn_exp2f(fmaf(x[k][e], c, -mc));
-                sum += (double)cs;
-            }
+            for (int e = 0; e < 4; ++e) cs += __builtin_amdgcn_exp2f(fmaf(x[e], c, -mc));
+            sum += (double)cs;
         }
     }
-    // the workgroup's part: (max a, sum exp(a - max a)), fixed order
-    __shared__ float s_m[kWalkThreads / kWave];
-    __shared__ double s_s[kWalkThreads / kWave];
-    __shared__ int s_nf;
-    if (threadIdx.x == 0) s_nf = 0;
-    const float wm = wave_max(m);
-    const double ws = wave_sum((m == -INFINITY || m == wm) ? (m == -INFINITY ? 0.0 : sum)
-                                                           : sum * (double)exp2f((m - wm) * c));
-    const int wnf = wave_or(nf ? 1 : 0);
-    __syncthreads();
-    if ((threadIdx.x % kWave) == 0) {
-        s_m[threadIdx.x / kWave] = wm;
-        s_s[threadIdx.x / kWave] = ws;
-        if (wnf) s_nf = 1;
-    }
-    __syncthreads();
-    float M = s_m[0];
-    for (int w = 1; w < kWalkThreads / kWave; ++w) M = fmaxf(M, s_m[w]);
-    double tot = 0.0;
-    if (M > -INFINITY && M < INFINITY)
-        for (int w = 0; w < kWalkThreads / kWave; ++w)
-            if (s_m[w] > -INFINITY) tot += s_s[w] * (double)exp2f((s_m[w] - M) * c);
-    const bool part_bad = s_nf != 0 || M == INFINITY || !isfinite(tot);
-    return X.lse(M > -INFINITY && !part_bad ? (double)(M * A.invT) : -INFINITY, part_bad ? 0.0 : tot, part_bad, bad);
+};
+
+template <int DT>
+__device__ __forceinline__ double entered_row_lse(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow,
+                                                  const RawRow<DT>& t, Exchange& X, const double* et,
+                                                  bool* bad) {
+    const float c = A.invT * 1.4426950408889634f;
+    RowPart p;
+    row_groups<DT>(A.target, vec, S, trow, t, 1.0f, [&](int, int, const float(&x)[4]) { p.add(x, c); });
+    return X.lse(p.m, p.sum, p.nf, c, A.invT, et, bad);
 }
 
 // Relative half-width of the band in which an acceptance test taken with the
@@ -570,118 +674,31 @@ __device__ double entered_row_lse(const WalkArgs& A, bool vec, const WalkSlice& 
 // normaliser is within ~1e-6 of it: binary32 terms, binary64 accumulation).
 constexpr double kDecisionBand = 1e-4;
 
-// The target and draft logits of a cached slice, loaded ahead of the pass
-// that needs them.
-constexpr int kFillGroups = (kWalkCache + 4 * kWalkThreads - 1) / (4 * kWalkThreads);
-template <int DT>
-struct FillRaw {
-    Raw4<DT> t[kFillGroups], d[kFillGroups];
+// First exact pass at a node: the thread's parts of sum p~, and, for the
+// first residual (C = 1), of sum p~ and sum q over tokens with p~ > q (beyond
+// the band where the normaliser could flip the sign) and the number of tokens
+// inside that band.
+struct FirstPass {
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    __device__ __forceinline__ void add(double pt, double qd) {
+        v[0] += pt;
+        if (pt > qd * (1.0 + 1e-5)) {
+            v[1] += pt;
+            v[2] += qd;
+        } else if (pt >= qd * (1.0 - 1e-5) && pt > 0.0) {
+            v[3] += 1.0;
+        }
+    }
 };
 
-template <int DT>
-__device__ __forceinline__ void fill_prefetch(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow,
-                                              size_t drow, FillRaw<DT>& f) {
-    const int n = S.v1 - S.v0;
-#pragma unroll
-    for (int k = 0; k < kFillGroups; ++k) {
-        const int i = (k * kWalkThreads + (int)threadIdx.x) * 4;
-        const int valid = max(0, min(4, n - i));
-        raw_load4<DT>(A.target, trow + S.v0 + (valid ? i : 0), valid, vec, f.t[k]);
-        raw_load4<DT>(A.draft, drow + S.v0 + (valid ? i : 0), valid, vec, f.d[k]);
-    }
-}
-
-// First exact pass at a node: fills (p~, q) and returns the slice partials of
-// sum p~, and, for the first residual (C = 1), sum p~ and sum q over tokens
-// with p~ > q (beyond the band where the normaliser could flip the sign) and
-// the number of tokens inside that band.
-template <int DT>
-__device__ void fill_pass(const WalkArgs& A, bool vec, const WalkSlice& S, bool cached, size_t trow, size_t drow,
-                          double L0, double Ld, const double* et, double (&out)[4]) {
-    double sp = 0.0, pa = 0.0, qa = 0.0, band = 0.0;
-    if (cached) {
-        // the whole slice fits the LDS cache: every load of the thread is
-        // issued before any arithmetic (one memory latency per pass)
-        const int n = S.v1 - S.v0;
-        FillRaw<DT> pre;
-        fill_prefetch<DT>(A, vec, S, trow, drow, pre);
-#pragma unroll
-        for (int k = 0; k < kFillGroups; ++k) {
-            const int i = (k * kWalkThreads + (int)threadIdx.x) * 4;
-            const int valid = max(0, min(4, n - i));
-            float at[4], ad[4];
-            raw_scaled4<DT>(pre.t[k], valid, A.invT, at);
-            raw_scaled4<DT>(pre.d[k], valid, A.invT, ad);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const double pt = at[e] > -INFINITY ? exp64((double)at[e] - L0, et) : 0.0;
-                const double qd = ad[e] > -INFINITY ? exp64((double)ad[e] - Ld, et) : 0.0;
-                sp += pt;
-                if (pt > qd * (1.0 + 1e-5)) {
-                    pa += pt;
-                    qa += qd;
-                } else if (pt >= qd * (1.0 - 1e-5) && pt > 0.0) {
-                    band += 1.0;
-                }
-                if (i + e < n) {
-                    S.p[i + e] = pt;
-                    S.q[i + e] = qd;
-                }
-            }
-        }
-    } else {
-        for (int c = 0; c < S.nchunks; ++c) {
-            const int c0 = S.v0 + c * kWalkCache;
-            const int n = min(kWalkCache, S.v1 - c0);
-            // one group of four tokens per iteration; the next group's loads are
-            // issued before this group's arithmetic
-            int i = (int)threadIdx.x * 4;
-            float at[4], ad[4];
-            {
-                const int valid = max(0, min(4, n - i));
-                load4_scaled<DT>(A.target, trow + c0 + (valid ? i : 0), valid, vec, A.invT, at);
-                load4_scaled<DT>(A.draft, drow + c0 + (valid ? i : 0), valid, vec, A.invT, ad);
-            }
-            for (; i < n; i += 4 * kWalkThreads) {
-                const int inext = i + 4 * kWalkThreads;
-                float nt[4], nd[4];
-                const int vn = max(0, min(4, n - inext));
-                load4_scaled<DT>(A.target, trow + c0 + (vn ? inext : 0), vn, vec, A.invT, nt);
-                load4_scaled<DT>(A.draft, drow + c0 + (vn ? inext : 0), vn, vec, A.invT, nd);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const double pt = at[e] > -INFINITY ? exp64((double)at[e] - L0, et) : 0.0;
-                    const double qd = ad[e] > -INFINITY ? exp64((double)ad[e] - Ld, et) : 0.0;
-                    sp += pt;
-                    if (pt > qd * (1.0 + 1e-5)) {
-                        pa += pt;
-                        qa += qd;
-                    } else if (pt >= qd * (1.0 - 1e-5) && pt > 0.0) {
-                        band += 1.0;
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    at[e] = nt[e];
-                    ad[e] = nd[e];
-                }
-            }
-        }
-    }
-    out[0] = sp;
-    out[1] = pa;
-    out[2] = qa;
-    out[3] = band;
-    walk_sum4(out);
-}
-
-// End of a walk, for every workgroup of the request: the request's outputs,
-// and the optional normaliser output (from the target stream's partials,
-// which the caller streamed when it asked for it). rows_bad < 0: every target
-// row of the tree must be usable (each workgroup checks the partials, so all
-// agree); otherwise rows_bad is the walk's own verdict on the rows it entered.
+// End of a walk: the request's outputs, and the optional normaliser output
+// (from the target stream's partials, which the caller streamed when it asked
+// for it). rows_bad < 0: every target row of the tree must be usable (from
+// the partials); otherwise rows_bad is the walk's own verdict on the rows it
+// entered.
 __device__ __forceinline__ void walk_tail(const WalkArgs& A, int r, int g, int G, int n, bool draft_bad, bool invalid, int nacc,
                           int bonus_out, int add_status, int tcount, int rows_bad = -1) {
+    if (g != 0 && !A.out.target_lse) return;  // uniform over the workgroup
     __shared__ int s_bad;
     const int tid = threadIdx.x;
     const int B1 = A.B + 1;
@@ -691,11 +708,8 @@ __device__ __forceinline__ void walk_tail(const WalkArgs& A, int r, int g, int G
     if (tid == 0) s_bad = 0;
     __syncthreads();
     if (!draft_bad && rows_bad < 0)
-        for (int i = tid; i < n; i += kWalkThreads) {
-            int b;
-            target_lse(A, r, i, &b);
-            if (b) atomicOr(&s_bad, 1);
-        }
+        for (int i = tid; i < n; i += kWalkThreads)
+            if (target_row_bad(A.tm, A.tf, A.S4, tb + i)) atomicOr(&s_bad, 1);
     __syncthreads();
     const bool bad = draft_bad || (rows_bad < 0 ? s_bad != 0 : rows_bad != 0);
     if (A.out.target_lse) {
@@ -733,19 +747,59 @@ __device__ __forceinline__ void walk_tail(const WalkArgs& A, int r, int g, int G
     }
 }
 
+// What a walk knows of a node it enters: its topology checks, normalisers and
+// children, one child per lane (every wave loads them for itself).
+struct Entered {
+    TreeNode t;
+    double L0, Ld;     // streamed target normaliser (where known), draft normaliser of the children's row
+    bool l0, row_bad;  // L0 and row_bad are known
+    int tok;           // child lane's token, and its draft and target logits x invT
+    float xd, xt;
+    int kids;          // child lane's own child count (traversal)
+};
+
+// Values that are the same in every lane, moved to scalar registers (the walks
+// keep about thirty of them, which would take half of a thread's vector
+// registers).
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ double uni(double x) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+__device__ __forceinline__ Entered enter_record(const uint32_t* nrec, size_t node, int lane) {
+    const uint32_t* rp = nrec + node * kRecWords;
+    const uint4 h0 = *(const uint4*)rp;
+    const uint4 h1 = *(const uint4*)(rp + 4);
+    const uint4 c = lane < TSB_MAX_K ? *(const uint4*)(rp + 8 + 4 * lane) : make_uint4(0u, 0u, 0u, 0u);
+    Entered e;
+    const int flags = uni((int)h0.w);
+    e.t.m = uni((int)h0.x);
+    e.t.fc = uni((int)h0.y);
+    e.t.d = uni((int)h0.z);
+    e.t.ok = (flags & (int)kRecOk) != 0;
+    e.row_bad = (flags & (int)kRecTargetBad) != 0;
+    e.l0 = (flags & (int)kRecNoL0) == 0;
+    e.L0 = uni(rec_f64(h1.x, h1.y));
+    e.Ld = uni(rec_f64(h1.z, h1.w));
+    e.tok = (int)c.x;
+    e.xd = __uint_as_float(c.y);
+    e.xt = __uint_as_float(c.z);
+    e.kids = (int)c.w;
+    return e;
+}
+
 template <int DT, bool VEC>
-__global__ __launch_bounds__(kWalkThreads) void verify_walk(WalkArgs A) {
-    extern __shared__ double s_pq[];  // [2 * kWalkCache]: p~ then q
+__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4))) void verify_walk(WalkArgs A) {
+    extern __shared__ double s_pq[];  // (p~, q) of the slice
     __shared__ double s_exp[kExpTable];
-    __shared__ int s_tok[TSB_MAX_K];
-    __shared__ float s_xd[TSB_MAX_K], s_xt[TSB_MAX_K];
-    __shared__ double s_u[TSB_MAX_K];
-    __shared__ int s_badtok;
     const int G = A.G;
     const int ticket = xticket(A.X, A.R);
     const int g = ticket % G;
     const int r = ticket / G;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid % kWave;
     const int B1 = A.B + 1;
     const size_t tb = (size_t)r * B1;
     const bool vec = VEC;
@@ -754,21 +808,10 @@ __global__ __launch_bounds__(kWalkThreads) void verify_walk(WalkArgs A) {
     const bool count_ok = tree_count_ok(n_raw, A.B);
     const int n = count_ok ? n_raw : 0;
     const bool lead = (g == 0 && tid == 0);
-    if (tid == 0) s_badtok = 0;
     exp64_table_init(s_exp);
 
-    // vocabulary slice (start a multiple of 4; an empty slice is [0, 0))
-    WalkSlice S;
-    {
-        const int span = ((A.V + G - 1) / G + 3) & ~3;
-        const bool has = (long long)g * span < A.V;
-        S.v0 = has ? g * span : 0;
-        S.v1 = has ? min(A.V, S.v0 + span) : 0;
-        S.nchunks = (S.v1 - S.v0 + kWalkCache - 1) / kWalkCache;
-        S.p = s_pq;
-        S.q = s_pq + kWalkCache;
-    }
-    const bool cached = S.nchunks <= 1;
+    const WalkSlice S = walk_slice(A.V, g, G);
+    const HeldPQ pq{s_pq, S.groups};
     const bool draft_bad = (*status_p & TSB_REQ_NONFINITE) != 0;
 
     int tcount = 0;
@@ -786,93 +829,59 @@ __global__ __launch_bounds__(kWalkThreads) void verify_walk(WalkArgs A) {
         key.step = A.step;
         Exchange X{&A, r, g, G, 0u, 0};
         int u = 0;
+        bool from_p = false;  // the round ends with a bonus from p_u, normaliser from_L
+        double from_L = 0.0;
+        RawRow<DT> rt, rd;    // u's rows
         while (true) {
             ++n_entered;
             const size_t trow = ((size_t)r * B1 + u) * (size_t)A.V;
             // every workgroup reads the same entries, so all take the same exit
-            TreeNode nd;
-            double L0 = 0.0, Ld = 0.0;
-            bool row_bad = false;  // u's target row is unusable
-            uint4 crec = make_uint4(0u, 0u, 0u, 0u);  // child tid's (token, x_d, x_t) from the record
-            if (A.nrec) {
-                // the node's record: its topology, draft normaliser and
-                // children in one round trip
-                const uint32_t* rp = A.nrec + (tb + u) * kRecWords;
-                const uint4 h0 = *(const uint4*)rp;
-                const uint4 h1 = *(const uint4*)(rp + 4);
-                if (tid < TSB_MAX_K) crec = *(const uint4*)(rp + 8 + 4 * tid);
-                nd.m = (int)h0.x;
-                nd.fc = (int)h0.y;
-                nd.d = (int)h0.z;
-                nd.ok = (h0.w & kRecOk) != 0;
-                L0 = rec_f64(h1.x, h1.y);
-                row_bad = (h0.w & kRecTargetBad) != 0;
-                Ld = rec_f64(h1.z, h1.w);
-            } else {
-                nd = tree_node(A.tree, tb, u, n, A.D);
-                if (!A.reads_rows) {
-                    int tbad;
-                    L0 = target_lse(A, r, u, &tbad);
-                    row_bad = tbad != 0;
-                }
-            }
-            if (!nd.ok || (nd.m > 0 && nacc >= A.D)) {
+            Entered N = enter_record(A.nrec, tb + u, lane);
+            if (!N.t.ok || (N.t.m > 0 && nacc >= A.D)) {
                 add_status |= TSB_REQ_BAD_TREE;
                 invalid = true;
                 break;
             }
-            const int m = nd.m, d = nd.d;
-            // or the target row of u, read now that the walk has entered u: its
-            // streamed normaliser, and whether it is usable
+            const int m = N.t.m, fc = N.t.fc;
+            const size_t drow = ((size_t)r * A.D + (m > 0 ? N.t.d : 0)) * (size_t)A.V;
+            // the rows' slices are in flight while the normaliser and the first
+            // test are worked out
+            rt.load(A.target, vec, S, trow);
+            if (m > 0) rd.load(A.draft, vec, S, drow);
+            // the streamed normaliser of u's row, and whether the row is usable
             if (A.reads_rows) {
                 if (u < kChainRows) {  // the root or node 1: streamed before the walk
                     int tbad;
-                    L0 = target_row_lse(A.cm, A.cs, A.cf, kChainPieces, (size_t)r * kChainRows + u, &tbad);
-                    row_bad = tbad != 0;
+                    N.L0 = target_row_lse(A.cm, A.cs, A.cf, kChainPieces, (size_t)r * kChainRows + u, &tbad);
+                    N.row_bad = tbad != 0;
                 } else {
-                    L0 = entered_row_lse<DT>(A, vec, S, trow, X, &row_bad);
+                    N.L0 = entered_row_lse<DT>(A, vec, S, trow, rt, X, s_exp, &N.row_bad);
                 }
+            } else if (!N.l0) {
+                int tbad;
+                N.L0 = target_lse(A, r, u, &tbad);
+                N.row_bad = tbad != 0;
             }
-            if (row_bad) {
+            if (N.row_bad) {
                 rows_bad = 1;
                 break;
             }
-            const size_t drow = ((size_t)r * A.D + (m > 0 ? d : 0)) * (size_t)A.V;
+            const double L0 = uni(N.L0), Ld = N.Ld;
             if (m == 0) {  // accepted leaf: bonus from p_u
-                float bk;
-                int bi;
-                double unused;
-                bonus_from_p<DT>(A, vec, S, trow, L0, key, (uint32_t)u, &bk, &bi);
-                bonus_out = X.best(bk, bi, 0.0, &unused);
+                from_p = true;
+                from_L = L0;
                 break;
             }
-            if (!A.nrec) Ld = A.draft_lse[(size_t)r * A.D + d];
-            // children of u: tokens, their logits and the uniforms, fetched
-            // together; a token outside [0, V) is never used as an address
-            const int fc = nd.fc;
-            if (tid < m) {
-                if (A.nrec) {
-                    const int y = (int)crec.x;
-                    s_tok[tid] = y;
-                    s_xd[tid] = __uint_as_float(crec.y);
-                    s_xt[tid] = __uint_as_float(crec.z);
-                    if (!(y >= 0 && y < A.V)) s_badtok = 1;
-                } else {
-                    const int y = A.node_tok[tb + fc + tid];
-                    const bool yok = y >= 0 && y < A.V;
-                    s_tok[tid] = y;
-                    s_xd[tid] = yok ? load_logit<DT>(A.draft, drow + y) * A.invT : 0.f;
-                    s_xt[tid] = yok ? load_logit<DT>(A.target, trow + y) * A.invT : 0.f;
-                    if (!yok) s_badtok = 1;
-                }
-                s_u[tid] = u24d(rng_word(key, (uint32_t)(fc + tid), kStreamAccept, 0u));
-            }
-            __syncthreads();
-            if (s_badtok) {
+            // lane j: child j's uniform and probabilities; a token outside
+            // [0, V) is never used as an address
+            if (__ballot(lane < m && !(N.tok >= 0 && N.tok < A.V))) {
                 add_status |= TSB_REQ_BAD_TOKEN;
                 invalid = true;
                 break;
             }
+            const double ul = u24d(rng_word(key, (uint32_t)(fc + lane), kStreamAccept, 0u));
+            const double ql = exp64x((double)N.xd - Ld, s_exp);
+            double pl = exp64x((double)N.xt - L0, s_exp);
 
             bool exact = false;
             double Lt = L0, inv = 1.0;
@@ -880,12 +889,10 @@ __global__ __launch_bounds__(kWalkThreads) void verify_walk(WalkArgs A) {
             bool accepted = false, degenerate = false;
             for (int j = 0; j < m; ++j) {
                 const int c = fc + j;
-                const int y = s_tok[j];
-                const double qy = exp((double)s_xd[j] - Ld);
-                const double U = s_u[j];
-                const double W = Z / Sq;
-                double py = exp((double)s_xt[j] - Lt);
-                double num = py - C * qy;
+                const double qy = lane_f64(ql, j);
+                const double U = lane_f64(ul, j);
+                const double W = uni(Z / Sq);
+                double num = lane_f64(pl, j) - C * qy;
                 double ratio = (num > 0.0 ? num : 0.0) / (W * qy);
                 if (trace && tcount < TSB_TRACE_MAX) {
                     trace[tcount * 4 + 0] = c;
@@ -897,43 +904,50 @@ __global__ __launch_bounds__(kWalkThreads) void verify_walk(WalkArgs A) {
                 // the streamed normaliser; it stands if U is clear of the ratio by
                 // the band. A rejection needs the exact residual anyway.
                 if (!exact && (fabs(U - ratio) <= kDecisionBand * ratio || !(U < ratio))) {
-                    double part[4], tot[4];
-                    fill_pass<DT>(A, vec, S, cached, trow, drow, L0, Ld, s_exp, part);
-                    X.run<4>(part, tot);
-                    Lt = L0 + log(tot[0]);
-                    inv = 1.0 / tot[0];
+                    FirstPass f;
+                    if (S.held)
+                        pq.fill<DT>(A, vec, S, trow, drow, rt, rd, L0, Ld, s_exp, [&](double p, double q) { f.add(p, q); });
+                    else
+                        visit_pq<DT>(A, vec, S, trow, drow, L0, Ld, s_exp, [&](int, double p, double q) { f.add(p, q); });
+                    X.sum<4>(f.v);
+                    Lt = uni(L0 + log64(f.v[0], s_exp));
+                    inv = uni(1.0 / f.v[0]);
                     // first residual (C = 1): sum over {p > q} of p - q, exact when no
                     // token lies in the band where the normaliser decides the sign
-                    Z1 = tot[3] == 0.0 ? tot[1] * inv - tot[2] : -1.0;
+                    Z1 = uni(f.v[3] == 0.0 ? f.v[1] * inv - f.v[2] : -1.0);
                     exact = true;
-                    py = exp((double)s_xt[j] - Lt);
-                    num = py - C * qy;
+                    pl = exp64x((double)N.xt - Lt, s_exp);
+                    num = lane_f64(pl, j) - C * qy;
                     ratio = (num > 0.0 ? num : 0.0) / (W * qy);
                 }
                 if (trace && tcount <= TSB_TRACE_MAX) trace[(tcount - 1) * 4 + 2] = ratio;
                 if (U < ratio) {
                     if (lead) {
                         A.out.acc_node[(size_t)r * A.D + nacc] = c;
-                        A.out.acc_tok[(size_t)r * A.D + nacc] = y;
+                        A.out.acc_tok[(size_t)r * A.D + nacc] = (int)lane_u32((uint32_t)N.tok, j);
                     }
                     ++nacc;
                     u = c;
                     accepted = true;
                     break;
                 }
-                C = C + W;
-                Sq = Sq - qy;
+                C = uni(C + W);
+                Sq = uni(Sq - qy);
                 if (j + 1 == m) break;
                 // residual mass at the new C
                 if (j == 0 && Z1 >= 0.0) {
                     Z = Z1;
                 } else {
-                    double zp = 0.0;
-                    visit_pq<DT>(A, vec, S, cached, trow, drow, L0, inv, Ld, s_exp, [&](int, double p, double q) {
-                        const double rr = p - C * q;
-                        zp += rr > 0.0 ? rr : 0.0;
-                    });
-                    Z = X.sum(walk_sum(zp));
+                    double zp[1] = {0.0};
+                    if (S.held)
+                        zp[0] = pq.residual(S, inv, C);
+                    else
+                        visit_pq<DT>(A, vec, S, trow, drow, L0, Ld, s_exp, [&](int, double p, double q) {
+                            const double rr = p * inv - C * q;
+                            zp[0] += rr > 0.0 ? rr : 0.0;
+                        });
+                    X.sum<1>(zp);
+                    Z = uni(zp[0]);
                 }
                 if (trace && tcount <= TSB_TRACE_MAX) trace[(tcount - 1) * 4 + 3] = Z;
                 if (Z <= 0.0 || Sq <= 0.0) {
@@ -941,53 +955,13 @@ __global__ __launch_bounds__(kWalkThreads) void verify_walk(WalkArgs A) {
                     break;
                 }
             }
-            __syncthreads();  // s_tok & co. are rewritten at the next node
             if (accepted) continue;
             // every child rejected: bonus from the residual max(p - C q, 0)
             if (!degenerate) {
-                float best = -INFINITY;
-                int bidx = 0x7FFFFFFF;
-                double zp = 0.0;
-                const double Cc = C;
-                const uint32_t node = (uint32_t)u;
-                if (cached) {
-                    const int nn = S.v1 - S.v0;
-                    for (int i4 = tid; i4 * 4 < nn; i4 += kWalkThreads) {
-                        const uint4 w = rng_block(key, node, kStreamBonus, (uint32_t)((S.v0 >> 2) + i4));
-                        const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int i = i4 * 4 + e;
-                            if (i >= nn) break;
-                            const double rr = S.p[i] * inv - Cc * S.q[i];
-                            if (rr > 0.0) {
-                                zp += rr;
-                                const float kv = logf((float)rr) + gumbel_f32(ws[e]);
-                                const int v = S.v0 + i;
-                                if (kv > best || (kv == best && v < bidx)) {
-                                    best = kv;
-                                    bidx = v;
-                                }
-                            }
-                        }
-                    }
-                } else {
-                    visit_pq<DT>(A, vec, S, false, trow, drow, L0, inv, Ld, s_exp, [&](int v, double p, double q) {
-                        const double rr = p - Cc * q;
-                        if (rr > 0.0) {
-                            zp += rr;
-                            const float kv = logf((float)rr) + gumbel_f32(rng_word(key, node, kStreamBonus, (uint32_t)v));
-                            if (kv > best || (kv == best && v < bidx)) {
-                                best = kv;
-                                bidx = v;
-                            }
-                        }
-                    });
-                }
-                walk_argmax(&best, &bidx);
-                const double zs = walk_sum(zp);
-                double mass;
-                const int fi = X.best(best, bidx, zs, &mass);
+                double zp, mass;
+                const BestKey b = bonus_residual<DT>(A, vec, S, trow, drow, pq, L0, Ld, inv, C, s_exp, key,
+                                                     (uint32_t)u, zp);
+                const int fi = X.best(b, zp, &mass);
                 if (trace && tcount >= 1 && tcount <= TSB_TRACE_MAX) trace[(tcount - 1) * 4 + 3] = mass;
                 if (mass > 0.0 && fi >= 0) {
                     bonus_out = fi;
@@ -996,14 +970,16 @@ __global__ __launch_bounds__(kWalkThreads) void verify_walk(WalkArgs A) {
                 }
             }
             if (degenerate) {  // empty residual: bonus from p_u
-                float bk;
-                int bi;
-                double unused;
-                bonus_from_p<DT>(A, vec, S, trow, Lt, key, (uint32_t)u, &bk, &bi);
-                bonus_out = X.best(bk, bi, 0.0, &unused);
+                from_p = true;
+                from_L = Lt;
                 add_status |= TSB_REQ_DEGENERATE_RESIDUAL;
             }
             break;
+        }
+        if (from_p) {
+            const size_t trow = ((size_t)r * B1 + u) * (size_t)A.V;
+            double unused;
+            bonus_out = X.best(bonus_from_p<DT>(A, vec, S, trow, rt, from_L, key, (uint32_t)u), 0.0, &unused);
         }
         if (X.timeout) add_status |= TSB_REQ_WALK_TIMEOUT;
         if (A.stats && lead) {
@@ -1033,10 +1009,11 @@ __global__ __launch_bounds__(kWalkThreads) void verify_walk(WalkArgs A) {
 // Gumbel-max over the slice with the pool tokens left out (a bitmap of the
 // slice in LDS), merged with the pool tokens' residual keys.
 
-// Exact pass over the target row of the slice: sum of exp(a^t_v - L0).
+// Exact pass over the target row of the slice: the thread's part of the sum
+// of exp(a^t_v - L0).
 template <int DT>
-__device__ double target_pass(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow, double L0,
-                              const double* et) {
+__device__ __forceinline__ double target_pass(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow, double L0,
+                                              const double* et) {
     double sp = 0.0;
     const int n = S.v1 - S.v0;
     int i = (int)threadIdx.x * 4;
@@ -1045,29 +1022,27 @@ __device__ double target_pass(const WalkArgs& A, bool vec, const WalkSlice& S, s
         const int valid = max(0, min(4, n - i));
         load4_scaled<DT>(A.target, trow + S.v0 + (valid ? i : 0), valid, vec, A.invT, at);
     }
-    for (; i < n; i += 4 * kWalkThreads) {
-        const int inext = i + 4 * kWalkThreads;
+    for (; i < n; i += kWalkPass) {
+        const int inext = i + kWalkPass;
         float nt[4];
         const int vn = max(0, min(4, n - inext));
         load4_scaled<DT>(A.target, trow + S.v0 + (vn ? inext : 0), vn, vec, A.invT, nt);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sp += at[e] > -INFINITY ? exp64((double)at[e] - L0, et) : 0.0;
+        for (int e = 0; e < 4; ++e) sp += exp_or_0(at[e], L0, et);
 #pragma unroll
         for (int e = 0; e < 4; ++e) at[e] = nt[e];
     }
-    return walk_sum(sp);
+    return sp;
 }
 
 // Gumbel-max of ln p_v over the slice's tokens outside the pool.
 template <int DT>
-__device__ void bonus_off_pool(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow, double Lt,
-                               const RngKey& key, uint32_t node, const uint32_t* bits, float* bk, int* bi) {
-    float best = -INFINITY;
-    int bidx = 0x7FFFFFFF;
+__device__ __forceinline__ BestKey bonus_off_pool(const WalkArgs& A, bool vec, const WalkSlice& S, size_t trow,
+                                                  double Lt, const RngKey& key, uint32_t node, const uint32_t* bits) {
+    BestKey b;
     const SplitF Ls = split(Lt);
     const int n = S.v1 - S.v0;
-    for (int i4 = threadIdx.x; i4 * 4 < n; i4 += kWalkThreads) {
-        const int i = i4 * 4;
+    for (int i = (int)threadIdx.x * 4; i < n; i += kWalkPass) {
         const int valid = min(4, n - i);
         float at[4];
         load4_scaled<DT>(A.target, trow + S.v0 + i, valid, vec, A.invT, at);
@@ -1077,20 +1052,14 @@ __device__ void bonus_off_pool(const WalkArgs& A, bool vec, const WalkSlice& S, 
         for (int e = 0; e < 4; ++e) {
             if (e >= valid || at[e] == -INFINITY) continue;
             if ((bits[(i + e) >> 5] >> ((i + e) & 31)) & 1u) continue;  // a pool token
-            const float kv = ((at[e] - Ls.hi) - Ls.lo) + gumbel_f32(ws[e]);
-            const int v = S.v0 + i + e;
-            if (kv > best || (kv == best && v < bidx)) {
-                best = kv;
-                bidx = v;
-            }
+            b.offer(((at[e] - Ls.hi) - Ls.lo) + gumbel_f32(ws[e]), S.v0 + i + e);
         }
     }
-    *bk = best;
-    *bi = bidx;
+    return b;
 }
 
 template <int DT, bool VEC>
-__global__ __launch_bounds__(kWalkThreads) void verify_pool_walk(WalkArgs A) {
+__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4))) void verify_pool_walk(WalkArgs A) {
     extern __shared__ uint32_t s_bits[];  // pool membership over the slice
     __shared__ double s_exp[kExpTable];
     __shared__ int s_ptok[kPoolMax];
@@ -1118,16 +1087,7 @@ __global__ __launch_bounds__(kWalkThreads) void verify_pool_walk(WalkArgs A) {
     exp64_table_init(s_exp);
     if (tid == 0) s_badtok = 0;
 
-    WalkSlice S;
-    {
-        const int span = ((A.V + G - 1) / G + 3) & ~3;
-        const bool has = (long long)g * span < A.V;
-        S.v0 = has ? g * span : 0;
-        S.v1 = has ? min(A.V, S.v0 + span) : 0;
-        S.nchunks = 1;
-        S.p = nullptr;
-        S.q = nullptr;
-    }
+    const WalkSlice S = walk_slice(A.V, g, G);
     const int nwords = (S.v1 - S.v0 + 31) / 32;
     const bool draft_bad = (A.out.req_status[r] & TSB_REQ_NONFINITE) != 0;
 
@@ -1136,7 +1096,6 @@ __global__ __launch_bounds__(kWalkThreads) void verify_pool_walk(WalkArgs A) {
 
     int bonus_out = -1, add_status = count_ok ? 0 : TSB_REQ_BAD_TREE, nacc = 0;
     bool invalid = !count_ok;
-    int rows_bad = 0;  // an entered node's target row is unusable
     if (!draft_bad && count_ok) {
         RngKey key;
         key.k0 = A.k0;
@@ -1158,11 +1117,10 @@ __global__ __launch_bounds__(kWalkThreads) void verify_pool_walk(WalkArgs A) {
             int tbad;
             const double L0 = target_lse(A, r, u, &tbad);
             if (m == 0) {  // accepted leaf: bonus from p_u
-                float bk;
-                int bi;
                 double unused;
-                bonus_from_p<DT>(A, vec, S, trow, L0, key, (uint32_t)u, &bk, &bi);
-                bonus_out = X.best(bk, bi, 0.0, &unused);
+                RawRow<DT> rt;
+                rt.load(A.target, vec, S, trow);
+                bonus_out = X.best(bonus_from_p<DT>(A, vec, S, trow, rt, L0, key, (uint32_t)u), 0.0, &unused);
                 break;
             }
             // q_u over pool d, target logits at the pool tokens
@@ -1185,7 +1143,7 @@ __global__ __launch_bounds__(kWalkThreads) void verify_pool_walk(WalkArgs A) {
                 double q = 0.0;
                 if (zm > -INFINITY) {
                     const double e = z > -INFINITY ? exp64((double)z - (double)zm, s_exp) : 0.0;
-                    const double Lz = (double)zm + log(wave_sum(e));
+                    const double Lz = (double)zm + log64(wave_sum(e), s_exp);
                     q = z > -INFINITY ? exp64((double)z - Lz, s_exp) : 0.0;
                 }
                 if (lane < P) {
@@ -1226,7 +1184,7 @@ __global__ __launch_bounds__(kWalkThreads) void verify_pool_walk(WalkArgs A) {
                 const double qy = sl >= 0 ? s_q[sl] : 0.0;
                 const double U = s_u[j];
                 const double W = Z / Sq;
-                double py = s_xt[j] > -INFINITY ? exp((double)s_xt[j] - Lt) : 0.0;
+                double py = s_xt[j] > -INFINITY ? exp64x((double)s_xt[j] - Lt, s_exp) : 0.0;
                 double num = py - C * qy;
                 double ratio = qy > 0.0 ? (num > 0.0 ? num : 0.0) / (W * qy) : (py > 0.0 ? INFINITY : 0.0);
                 if (trace && tcount < TSB_TRACE_MAX) {
@@ -1236,8 +1194,10 @@ __global__ __launch_bounds__(kWalkThreads) void verify_pool_walk(WalkArgs A) {
                 }
                 ++tcount;
                 if (!exact && (fabs(U - ratio) <= kDecisionBand * ratio || !(U < ratio))) {
-                    Stot = X.sum(target_pass<DT>(A, vec, S, trow, L0, s_exp));
-                    Lt = L0 + log(Stot);
+                    double sp[1] = {target_pass<DT>(A, vec, S, trow, L0, s_exp)};
+                    X.sum<1>(sp);
+                    Stot = sp[0];
+                    Lt = L0 + log64(Stot, s_exp);
                     inv = 1.0 / Stot;
                     exact = true;
                     // pool probabilities p~_v with the same exponential as the pass
@@ -1247,7 +1207,7 @@ __global__ __launch_bounds__(kWalkThreads) void verify_pool_walk(WalkArgs A) {
                         if (lane < P) s_pp[lane] = pp;
                     }
                     __syncthreads();
-                    py = s_xt[j] > -INFINITY ? exp((double)s_xt[j] - Lt) : 0.0;
+                    py = s_xt[j] > -INFINITY ? exp64x((double)s_xt[j] - Lt, s_exp) : 0.0;
                     num = py - C * qy;
                     ratio = qy > 0.0 ? (num > 0.0 ? num : 0.0) / (W * qy) : (py > 0.0 ? INFINITY : 0.0);
                 }
@@ -1297,26 +1257,18 @@ __global__ __launch_bounds__(kWalkThreads) void verify_pool_walk(WalkArgs A) {
                     if (t >= S.v0 && t < S.v1) atomicOr(&s_bits[(t - S.v0) >> 5], 1u << ((t - S.v0) & 31));
                 }
                 __syncthreads();
-                float best;
-                int bidx;
-                bonus_off_pool<DT>(A, vec, S, trow, Lt, key, (uint32_t)u, s_bits, &best, &bidx);
+                BestKey b = bonus_off_pool<DT>(A, vec, S, trow, Lt, key, (uint32_t)u, s_bits);
                 if (tid < P) {
                     const int t = s_ptok[tid];
                     if (t >= S.v0 && t < S.v1) {
                         const double rr = s_pp[tid] * inv - C * s_q[tid];
                         if (rr > 0.0) {
-                            const float kv = logf((float)rr) +
-                                             gumbel_f32(rng_word(key, (uint32_t)u, kStreamBonus, (uint32_t)t));
-                            if (kv > best || (kv == best && t < bidx)) {
-                                best = kv;
-                                bidx = t;
-                            }
+                            b.offer(logf((float)rr) + gumbel_f32(rng_word(key, (uint32_t)u, kStreamBonus, (uint32_t)t)), t);
                         }
                     }
                 }
-                walk_argmax(&best, &bidx);
                 double unused;
-                const int fi = X.best(best, bidx, 0.0, &unused);
+                const int fi = X.best(b, 0.0, &unused);
                 if (fi >= 0) {
                     bonus_out = fi;
                 } else {
@@ -1324,11 +1276,10 @@ __global__ __launch_bounds__(kWalkThreads) void verify_pool_walk(WalkArgs A) {
                 }
             }
             if (degenerate) {  // empty residual: bonus from p_u
-                float bk;
-                int bi;
                 double unused;
-                bonus_from_p<DT>(A, vec, S, trow, Lt, key, (uint32_t)u, &bk, &bi);
-                bonus_out = X.best(bk, bi, 0.0, &unused);
+                RawRow<DT> rt;
+                rt.load(A.target, vec, S, trow);
+                bonus_out = X.best(bonus_from_p<DT>(A, vec, S, trow, rt, Lt, key, (uint32_t)u), 0.0, &unused);
                 add_status |= TSB_REQ_DEGENERATE_RESIDUAL;
             }
             break;
@@ -1362,36 +1313,37 @@ __global__ __launch_bounds__(kWalkThreads) void verify_pool_walk(WalkArgs A) {
 // Z' = T, alpha' = T / (T + 1 - alpha), S' = S - q(y).
 // The traversal is post-order (the first remaining child first, down to a
 // node with none left, which is tested with U < alpha); the root has
-// alpha = 1 and is accepted once its children are all rejected. One
-// (p~, q) slice is kept in LDS: that of the node the last pass was over, so
-// consecutive rejections among the children of one node reuse it.
-struct TravEntry {
-    int node, left;
-    double alpha, A, C, Z, S, L;  // L: binary64 log normaliser of the node's target row, NaN until computed
+// alpha = 1 and is accepted once its children are all rejected. The (p~, q)
+// slice held is that of the node the last pass was over, so consecutive
+// rejections among the children of one node reuse it.
+//
+// Bound by latency: a request's tests follow one another (up to one per node,
+// 128 in the slowest of 16 requests of 128 nodes, where the others take one),
+// each with a pass over the slice and an exchange. Everything else a test
+// needs is in registers when it is reached: a node's children (tokens, logits,
+// uniforms, probabilities, whether they are leaves) come with its record, one
+// child a lane, and a leaf is tested without entering it.
+// The node the traversal is at, the same in every thread. The states of its
+// ancestors wait on a stack in LDS; the node's children (Entered) and its
+// slice's (p~, q) are held in registers and read again when the traversal
+// comes back to it.
+struct TravState {
+    int node, left;       // left: children rejected so far
+    double alpha, A, C, Z, S;
+    double L;             // binary64 log normaliser of the node's target row, NaN until computed
+    double qself, uself;  // the node's own token's draft probability and uniform (as a child)
 };
-constexpr int kTravStack = TSB_MAX_D + 1;  // root .. depth D
-
-// (p~, q) of a node's slice into the LDS cache when the slice fits, and the
-// block sum of p~ = exp(a^t - L0) over the slice.
-template <int DT>
-__device__ double trav_fill(const WalkArgs& A, bool vec, const WalkSlice& S, bool cached, size_t trow, size_t drow,
-                            double L0, double Ld, const double* et) {
-    double acc = 0.0;
-    for (int c = 0; c < S.nchunks; ++c) acc += fill_chunk<DT>(A, vec, S, c, trow, drow, L0, Ld, et, cached);
-    return walk_sum(acc);
-}
 
 template <int DT, bool VEC>
-__global__ __launch_bounds__(kWalkThreads) void verify_traversal(WalkArgs A) {
-    extern __shared__ double s_pq[];  // [2 * kWalkCache]: p~ then q of the cached node
+__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4))) void verify_traversal(WalkArgs A) {
+    extern __shared__ double s_dyn[];  // the stack, root .. depth D, then (p~, q) of the slice
     __shared__ double s_exp[kExpTable];
-    __shared__ TravEntry s_stk[kTravStack];
-    __shared__ int s_cache;  // node whose slice is in the cache, -1 for none
+    TravState* const s_stk = (TravState*)s_dyn;
     const int G = A.G;
     const int ticket = xticket(A.X, A.R);
     const int g = ticket % G;
     const int r = ticket / G;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid % kWave;
     const int B1 = A.B + 1;
     const size_t tb = (size_t)r * B1;
     const bool vec = VEC;
@@ -1400,27 +1352,16 @@ __global__ __launch_bounds__(kWalkThreads) void verify_traversal(WalkArgs A) {
     const bool count_ok = tree_count_ok(n_raw, A.B);
     const int n = count_ok ? n_raw : 0;
     const bool lead = (g == 0 && tid == 0);
-    if (tid == 0) s_cache = -1;
     exp64_table_init(s_exp);
 
-    WalkSlice S;
-    {
-        const int span = ((A.V + G - 1) / G + 3) & ~3;
-        const bool has = (long long)g * span < A.V;
-        S.v0 = has ? g * span : 0;
-        S.v1 = has ? min(A.V, S.v0 + span) : 0;
-        S.nchunks = (S.v1 - S.v0 + kWalkCache - 1) / kWalkCache;
-        S.p = s_pq;
-        S.q = s_pq + kWalkCache;
-    }
-    const bool cached = S.nchunks <= 1;
+    const WalkSlice S = walk_slice(A.V, g, G);
+    const HeldPQ pq{s_dyn + (A.D + 1) * (sizeof(TravState) / sizeof(double)), S.groups};
     const bool draft_bad = (*status_p & TSB_REQ_NONFINITE) != 0;
 
     int tcount = 0;
     double* const trace = (lead && A.out.trace) ? A.out.trace + (size_t)r * TSB_TRACE_MAX * 4 : nullptr;
     int bonus_out = -1, add_status = count_ok ? 0 : TSB_REQ_BAD_TREE, nacc = 0;
     bool invalid = !count_ok;
-    int rows_bad = 0;  // an entered node's target row is unusable
     if (!draft_bad && count_ok) {
         RngKey key;
         key.k0 = A.k0;
@@ -1428,189 +1369,207 @@ __global__ __launch_bounds__(kWalkThreads) void verify_traversal(WalkArgs A) {
         key.request = (uint32_t)r;
         key.step = A.step;
         Exchange X{&A, r, g, G, 0u, 0};
-        if (tid == 0) s_stk[0] = TravEntry{0, 0, 1.0, 1.0, 0.0, 1.0, 1.0, (double)NAN};
-        __syncthreads();
         int top = 0;
-        // end of the round at the node on top of the stack: bonus from Mb (or
-        // from p on an empty residual) and the accepted path = stack[1 .. top]
-        int end_kind = 0;  // 1: bonus from Mb of the top node, 2: degenerate (bonus from p)
+        TravState E;
+        Entered N;
+        double ul = 0.0, pl = 0.0, ql = 0.0;  // lane j: child j's uniform and probabilities
+        RawRow<DT> rt, rd;
+        bool raw = false, filled = false;  // the slice's logits, its (p~, q) are E.node's
+        const auto rows = [&](int u, int d, size_t& trow, size_t& drow) {
+            trow = ((size_t)r * B1 + u) * (size_t)A.V;
+            drow = ((size_t)r * A.D + d) * (size_t)A.V;
+        };
+        // children of E.node, from its record
+        const auto children = [&]() {
+            N = enter_record(A.nrec, tb + E.node, lane);
+            if (!N.l0) {
+                int tbad;
+                N.L0 = uni(target_lse(A, r, E.node, &tbad));
+            }
+            ul = u24d(rng_word(key, (uint32_t)(N.t.fc + lane), kStreamAccept, 0u));
+            raw = filled = false;
+        };
+        const auto load_rows = [&]() {
+            if (raw) return;
+            size_t trow, drow;
+            rows(E.node, N.t.d, trow, drow);
+            rt.load(A.target, vec, S, trow);
+            rd.load(A.draft, vec, S, drow);
+            raw = true;
+        };
+        const auto probabilities = [&]() {
+            ql = exp64x((double)N.xd - N.Ld, s_exp);
+            pl = exp64x((double)N.xt - E.L, s_exp);
+        };
+        // the slice's (p~, q) of E.node (nothing if they are held already);
+        // returns the thread's sum of p~ then evaluated
+        const auto fill = [&]() -> double {
+            if (!S.held || filled) return 0.0;
+            load_rows();
+            size_t trow, drow;
+            rows(E.node, N.t.d, trow, drow);
+            double sp = 0.0;
+            pq.fill<DT>(A, vec, S, trow, drow, rt, rd, N.L0, N.Ld, s_exp, [&](double p, double) { sp += p; });
+            filled = true;
+            return sp;
+        };
+        E = TravState{0, 0, 1.0, 1.0, 0.0, 1.0, 1.0, (double)NAN, 1.0, 0.0};
+        children();
+        // end of the round: 1: bonus from Mb of E.node (or of the accepted leaf), 2: degenerate (bonus from p)
+        int end_kind = 0;
+        int leaf = -1;  // an accepted leaf child of E.node
         while (true) {
-            const TravEntry E = s_stk[top];
-            const int u = E.node;
             // every workgroup reads the same entries, so all take the same exits
-            const TreeNode nd = tree_node(A.tree, tb, u, n, A.D);
-            if (!nd.ok) {
+            if (!N.t.ok) {
                 add_status |= TSB_REQ_BAD_TREE;
                 invalid = true;
                 break;
             }
-            const size_t trow = ((size_t)r * B1 + u) * (size_t)A.V;
-            if (E.left < nd.m) {  // descend to the next remaining child of u
+            double qy;           // the rejected child's draft probability
+            if (E.left < N.t.m) {  // descend to the next remaining child
                 if (top + 1 > A.D) {
                     add_status |= TSB_REQ_BAD_TREE;
                     invalid = true;
                     break;
                 }
-                const size_t drow = ((size_t)r * A.D + nd.d) * (size_t)A.V;
-                const double Ld = A.draft_lse[(size_t)r * A.D + nd.d];
-                double L = E.L;
-                if (isnan(L)) {  // first descent from u: binary64 normaliser of its target row
-                    int tbad;
-                    const double L0 = target_lse(A, r, u, &tbad);
-                    const double tot = X.sum(trav_fill<DT>(A, vec, S, cached, trow, drow, L0, Ld, s_exp));
-                    L = L0 + log(tot);
-                    if (tid == 0) {
-                        s_stk[top].L = L;
-                        s_cache = cached ? u : -1;
+                if (isnan(E.L)) {  // first descent: binary64 normaliser of the node's target row
+                    double s[1] = {0.0};
+                    if (S.held) {
+                        s[0] = fill();
+                    } else {
+                        size_t trow, drow;
+                        rows(E.node, N.t.d, trow, drow);
+                        visit_pq<DT>(A, vec, S, trow, drow, N.L0, N.Ld, s_exp, [&](int, double p, double) { s[0] += p; });
                     }
+                    X.sum<1>(s);
+                    E.L = uni(N.L0 + log64(s[0], s_exp));
+                    probabilities();
                 }
-                const int c = nd.fc + E.left;
-                const int y = A.node_tok[tb + c];
+                const int c = N.t.fc + E.left;
+                const int y = (int)lane_u32((uint32_t)N.tok, E.left);
                 if (y < 0 || y >= A.V) {
                     add_status |= TSB_REQ_BAD_TOKEN;
                     invalid = true;
                     break;
                 }
-                const double py = exp((double)(load_logit<DT>(A.target, trow + y) * A.invT) - L);
-                const double qy = exp((double)(load_logit<DT>(A.draft, drow + y) * A.invT) - Ld);
-                const double num = E.A * py - E.C * qy;  // Z Mb_u(y) before the max
-                const double ms = qy / E.S;             // Ms_u(y)
+                qy = lane_f64(ql, E.left);
+                const double num = E.A * lane_f64(pl, E.left) - E.C * qy;  // Z Mb_u(y) before the max
+                const double ms = qy / E.S;                                // Ms_u(y)
                 double ac;
                 if (!(ms > 0.0))
                     ac = (num > 0.0 && E.alpha > 0.0) ? 1.0 : 0.0;
                 else
                     ac = num > 0.0 ? fmin(1.0, E.alpha * (num / E.Z) / ms) : 0.0;
-                __syncthreads();  // every thread has read s_stk[top] and s_cache
-                if (tid == 0) s_stk[top + 1] = TravEntry{c, 0, ac, 1.0, 0.0, 1.0, 1.0, (double)NAN};
-                __syncthreads();
-                ++top;
-                continue;
+                ac = uni(ac);
+                const double U = lane_f64(ul, E.left);
+                if ((int)lane_u32((uint32_t)N.kids, E.left) != 0) {
+                    // a child with children of its own: its state waits for theirs
+                    __syncthreads();  // the stack's entry may still be read
+                    if (tid == 0) s_stk[top] = E;
+                    __syncthreads();
+                    ++top;
+                    E = TravState{c, 0, ac, 1.0, 0.0, 1.0, 1.0, (double)NAN, qy, U};
+                    children();
+                    if (N.t.ok && N.t.m > 0) load_rows();
+                    continue;
+                }
+                // a leaf: tested on the spot
+                if (trace && tcount < TSB_TRACE_MAX) {
+                    trace[tcount * 4 + 0] = c;
+                    trace[tcount * 4 + 1] = U;
+                    trace[tcount * 4 + 2] = ac;
+                    trace[tcount * 4 + 3] = -1.0;
+                }
+                ++tcount;
+                if (U < ac) {
+                    leaf = c;
+                    end_kind = 1;
+                    break;
+                }
+            } else {
+                if (top == 0) {  // every child of the root rejected: the root is accepted
+                    end_kind = 1;
+                    break;
+                }
+                // test the node: accept the path root .. node with probability alpha
+                if (trace && tcount < TSB_TRACE_MAX) {
+                    trace[tcount * 4 + 0] = E.node;
+                    trace[tcount * 4 + 1] = E.uself;
+                    trace[tcount * 4 + 2] = E.alpha;
+                    trace[tcount * 4 + 3] = -1.0;
+                }
+                ++tcount;
+                if (E.uself < E.alpha) {
+                    end_kind = 1;
+                    break;
+                }
+                qy = E.qself;
+                --top;
+                {
+                    const TravState w = s_stk[top];
+                    E = TravState{uni(w.node), uni(w.left), uni(w.alpha), uni(w.A), uni(w.C), uni(w.Z),
+                                  uni(w.S), uni(w.L), uni(w.qself), uni(w.uself)};
+                }
+                children();
+                load_rows();
+                probabilities();
             }
-            if (top == 0) {  // every child of the root rejected: the root is accepted
-                end_kind = 1;
-                break;
+            // the child was rejected: update E with the quantities it was drawn from
+            const double A2 = uni(E.alpha * E.A / E.Z);
+            const double C2 = uni(E.alpha * E.C / E.Z + 1.0 / E.S);
+            const double inv = uni(exp64x(N.L0 - E.L, s_exp));
+            double z[1] = {0.0};
+            if (S.held) {
+                fill();
+                z[0] = pq.residual(S, A2 * inv, C2);
+            } else {
+                size_t trow, drow;
+                rows(E.node, N.t.d, trow, drow);
+                visit_pq<DT>(A, vec, S, trow, drow, N.L0, N.Ld, s_exp, [&](int, double p, double q) {
+                    const double rr = p * (A2 * inv) - C2 * q;
+                    z[0] += rr > 0.0 ? rr : 0.0;
+                });
             }
-            // test u: accept the path root .. u with probability alpha_u
-            const double U = u24d(rng_word(key, (uint32_t)u, kStreamAccept, 0u));
-            if (trace && tcount < TSB_TRACE_MAX) {
-                trace[tcount * 4 + 0] = u;
-                trace[tcount * 4 + 1] = U;
-                trace[tcount * 4 + 2] = E.alpha;
-                trace[tcount * 4 + 3] = -1.0;
-            }
-            ++tcount;
-            if (U < E.alpha) {
-                end_kind = 1;
-                break;
-            }
-            // u rejected: update its parent w with the quantities u was drawn from
-            const TravEntry W = s_stk[top - 1];
-            const int w = W.node;
-            const TreeNode nw = tree_node(A.tree, tb, w, n, A.D);  // checked when it was descended from
-            const size_t trow_w = ((size_t)r * B1 + w) * (size_t)A.V;
-            const size_t drow_w = ((size_t)r * A.D + nw.d) * (size_t)A.V;
-            const double Ld = A.draft_lse[(size_t)r * A.D + nw.d];
-            int tbad;
-            const double L0 = target_lse(A, r, w, &tbad);
-            const int yu = A.node_tok[tb + u];
-            const double qy = exp((double)(load_logit<DT>(A.draft, drow_w + yu) * A.invT) - Ld);
-            const double A2 = W.alpha * W.A / W.Z;
-            const double C2 = W.alpha * W.C / W.Z + 1.0 / W.S;
-            const bool hit = cached && s_cache == w;
-            __syncthreads();  // every thread has read s_stk and s_cache
-            if (cached && !hit) {
-                trav_fill<DT>(A, vec, S, true, trow_w, drow_w, L0, Ld, s_exp);
-                if (tid == 0) s_cache = w;
-            }
-            const double inv = exp(L0 - W.L);
-            double zp = 0.0;
-            visit_pq<DT>(A, vec, S, cached, trow_w, drow_w, L0, inv, Ld, s_exp, [&](int, double p, double q) {
-                const double rr = A2 * p - C2 * q;
-                zp += rr > 0.0 ? rr : 0.0;
-            });
-            const double T = X.sum(walk_sum(zp));
+            X.sum<1>(z);
+            const double T = uni(z[0]);
             if (trace && tcount <= TSB_TRACE_MAX) trace[(tcount - 1) * 4 + 3] = T;
-            const int left = W.left + 1;
-            const double S2 = W.S - qy;
-            --top;
-            if ((T <= 0.0 && W.alpha >= 1.0) || (S2 <= 0.0 && left < nw.m)) {
+            const int left = E.left + 1;
+            const double S2 = uni(E.S - qy);
+            if ((T <= 0.0 && E.alpha >= 1.0) || (S2 <= 0.0 && left < N.t.m)) {
                 end_kind = 2;
                 break;
             }
-            if (tid == 0) {
-                TravEntry& e = s_stk[top];
-                e.left = left;
-                e.S = S2;
-                if (T > 0.0) {
-                    e.alpha = T / (T + (1.0 - W.alpha));
-                    e.A = A2;
-                    e.C = C2;
-                    e.Z = T;
-                } else {
-                    e.alpha = 0.0;
-                    e.A = 0.0;
-                    e.C = 0.0;
-                    e.Z = 1.0;
-                }
+            E.left = left;
+            E.S = S2;
+            if (T > 0.0) {
+                E.alpha = uni(T / (T + (1.0 - E.alpha)));
+                E.A = A2;
+                E.C = C2;
+                E.Z = T;
+            } else {
+                E.alpha = 0.0;
+                E.A = 0.0;
+                E.C = 0.0;
+                E.Z = 1.0;
             }
-            __syncthreads();
         }
         if (end_kind != 0) {
-            const TravEntry E = s_stk[top];
-            const int u = E.node;
-            const TreeNode nd = tree_node(A.tree, tb, u, n, A.D);
+            const int u = leaf >= 0 ? leaf : E.node;
             const size_t trow = ((size_t)r * B1 + u) * (size_t)A.V;
-            int tbad;
-            const double L0 = target_lse(A, r, u, &tbad);
-            bool from_p = end_kind == 2 || E.left == 0;  // a node whose residual was never formed: Mb = p
+            // a node whose residual was never formed: Mb = p
+            bool from_p = end_kind == 2 || leaf >= 0 || E.left == 0;
             if (!from_p) {
                 // Gumbel-max of ln max(p - (C / A) q, 0) (the positive factor A and the normaliser Z shift
                 // every key alike)
-                const size_t drow = ((size_t)r * A.D + nd.d) * (size_t)A.V;
-                const double Ld = A.draft_lse[(size_t)r * A.D + nd.d];
+                size_t tr, dr;
+                rows(E.node, N.t.d, tr, dr);
                 const double lam = E.C / E.A;
-                const bool hit = cached && s_cache == u;
-                __syncthreads();
-                if (cached && !hit) trav_fill<DT>(A, vec, S, true, trow, drow, L0, Ld, s_exp);
-                const double inv = exp(L0 - E.L);
-                float best = -INFINITY;
-                int bidx = 0x7FFFFFFF;
-                const uint32_t node = (uint32_t)u;
-                if (cached) {
-                    const int nn = S.v1 - S.v0;
-                    for (int i4 = tid; i4 * 4 < nn; i4 += kWalkThreads) {
-                        const uint4 wv = rng_block(key, node, kStreamBonus, (uint32_t)((S.v0 >> 2) + i4));
-                        const uint32_t ws[4] = {wv.x, wv.y, wv.z, wv.w};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int i = i4 * 4 + e;
-                            if (i >= nn) break;
-                            const double rr = S.p[i] * inv - lam * S.q[i];
-                            if (rr > 0.0) {
-                                const float kv = logf((float)rr) + gumbel_f32(ws[e]);
-                                const int v = S.v0 + i;
-                                if (kv > best || (kv == best && v < bidx)) {
-                                    best = kv;
-                                    bidx = v;
-                                }
-                            }
-                        }
-                    }
-                } else {
-                    visit_pq<DT>(A, vec, S, false, trow, drow, L0, inv, Ld, s_exp, [&](int v, double p, double q) {
-                        const double rr = p - lam * q;
-                        if (rr > 0.0) {
-                            const float kv = logf((float)rr) + gumbel_f32(rng_word(key, node, kStreamBonus, (uint32_t)v));
-                            if (kv > best || (kv == best && v < bidx)) {
-                                best = kv;
-                                bidx = v;
-                            }
-                        }
-                    });
-                }
-                walk_argmax(&best, &bidx);
-                double unused;
-                const int fi = X.best(best, bidx, 0.0, &unused);
+                const double inv = exp64x(N.L0 - E.L, s_exp);
+                fill();
+                double unused_mass, unused;
+                const BestKey b = bonus_residual<DT>(A, vec, S, tr, dr, pq, N.L0, N.Ld, inv, lam, s_exp, key,
+                                                         (uint32_t)u, unused_mass);
+                const int fi = X.best(b, 0.0, &unused);
                 if (fi >= 0) {
                     bonus_out = fi;
                 } else {
@@ -1619,17 +1578,21 @@ __global__ __launch_bounds__(kWalkThreads) void verify_traversal(WalkArgs A) {
                 }
             }
             if (from_p) {
-                float bk;
-                int bi;
+                double L = E.L;
+                if (leaf >= 0 || isnan(L)) {
+                    int tbad;
+                    L = target_lse(A, r, u, &tbad);
+                }
+                RawRow<DT> t;
+                t.load(A.target, vec, S, trow);
                 double unused;
-                bonus_from_p<DT>(A, vec, S, trow, isnan(E.L) ? L0 : E.L, key, (uint32_t)u, &bk, &bi);
-                bonus_out = X.best(bk, bi, 0.0, &unused);
+                bonus_out = X.best(bonus_from_p<DT>(A, vec, S, trow, t, L, key, (uint32_t)u), 0.0, &unused);
             }
             if (end_kind == 2) add_status |= TSB_REQ_DEGENERATE_RESIDUAL;
-            nacc = top;
+            nacc = top + (leaf >= 0 ? 1 : 0);
             if (lead)
-                for (int i = 1; i <= top; ++i) {
-                    const int c = s_stk[i].node;
+                for (int i = 1; i <= nacc; ++i) {
+                    const int c = i == top + 1 ? leaf : (i == top ? E.node : s_stk[i].node);
                     A.out.acc_node[(size_t)r * A.D + i - 1] = c;
                     A.out.acc_tok[(size_t)r * A.D + i - 1] = A.node_tok[tb + c];
                 }
@@ -1640,13 +1603,8 @@ __global__ __launch_bounds__(kWalkThreads) void verify_traversal(WalkArgs A) {
 }
 
 // ------------------------------------------------------------------ launch
-// Workgroups of the walk that are resident at once on the current device
-// (one per CU: the LDS cache fills a CU). Every launch of the walk stays
-// within this, in order of requests, so all workgroups of a launch run
-// together and every exchange completes; the bounded polling of an exchange
-// turns a device shared with other work (workgroups kept waiting) into
-// TSB_REQ_WALK_TIMEOUT instead of a hang. Queried once per (device,
-// kernel instance).
+// Workgroups of the walk that fit on the current device at once (the tickets
+// need the G of one request to). Queried once per (device, kernel instance).
 static hipError_t walk_capacity(const void* fn, int kind, int dt, int vec, size_t lds, int* cap) {
     constexpr int kDevs = 64;
     static std::atomic<int> cached[kDevs][3][2][2];
@@ -1697,8 +1655,10 @@ TargetJob target_job(const tsb_config& c, const void* target, const tsb_tree& tr
     return j;
 }
 
+// With a record job, workgroups after the chunks' write the walk's node
+// records (without the normalisers, which only the chunks hold).
 static hipError_t launch_target_partials(const tsb_config& c, float invT, const void* target, const tsb_tree& tree,
-                                         const VerifyWs& w, char* ws, hipStream_t st) {
+                                         const VerifyWs& w, char* ws, hipStream_t st, const RecordJob& rec) {
     TargetJob j = target_job(c, target, tree, nullptr, ws);
     j.tm = (float*)(ws + w.tm);
     j.ts = (double*)(ws + w.ts);
@@ -1709,34 +1669,49 @@ static hipError_t launch_target_partials(const tsb_config& c, float invT, const 
     if (e != hipSuccess) return e;
     auto fn = c.dtype == TSB_BF16 ? (j.vec ? target_partials<TSB_BF16, true> : target_partials<TSB_BF16, false>)
                                   : (j.vec ? target_partials<TSB_F32, true> : target_partials<TSB_F32, false>);
-    fn<<<j.ngroups, kBlock, 0, st>>>(target, c.V, c.B, j.nrows, j.chunk, j.P, invT, j.n_nodes, j.tm, j.ts, j.tf, X,
-                                     c.R);
+    fn<<<j.ngroups + record_blocks(rec, kBlock), kBlock, 0, st>>>(target, c.V, c.B, j.nrows, j.chunk, j.P, invT,
+                                                                  j.n_nodes, j.tm, j.ts, j.tf, X, c.R, j.ngroups, rec);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return hook_after(TSB_KERNEL_TARGET_PARTIALS, st);
 }
 
 // Rows 0 and 1 of every request for a walk that reads the other rows itself
-// (tsb_verify; a round streams them beside the planner), and the clearing of
-// the walk's exchange slots. No profiling id: tsb_profile_kernel's target
+// (tsb_verify; a round streams them beside the planner), the clearing of the
+// walk's exchange slots and, on the workgroups after those, its node records. No profiling id: tsb_profile_kernel's target
 // stream is target_partials alone.
 template <int DT, bool VEC>
-__global__ __launch_bounds__(kChainThreads) void chain_rows(ChainJob cj, XRegion X, int R, float invT) {
-    xclear(X, R, (size_t)blockIdx.x * kChainThreads + threadIdx.x, (size_t)gridDim.x * kChainThreads);
-    for (int g = blockIdx.x; g < cj.items; g += gridDim.x)
+__global__ __launch_bounds__(kChainThreads) void chain_rows(ChainJob cj, XRegion X, int R, float invT, int nchain,
+                                                            RecordJob rec) {
+    if ((int)blockIdx.x >= nchain) {
+        record_block<DT>(rec, (int)blockIdx.x - nchain, invT);
+        return;
+    }
+    xclear(X, R, (size_t)blockIdx.x * kChainThreads + threadIdx.x, (size_t)nchain * kChainThreads);
+    for (int g = blockIdx.x; g < cj.items; g += nchain)
         chain_piece<DT, VEC>(g, cj.target, cj.V, cj.B, invT, cj.cm, cj.cs, cj.cf);
 }
 
-static hipError_t launch_chain_rows(const tsb_config& c, float invT, const void* target, char* ws, hipStream_t st) {
+static hipError_t launch_chain_rows(const tsb_config& c, float invT, const void* target, char* ws, hipStream_t st,
+                                    const RecordJob& rec) {
     const ChainJob j = chain_job(c, target, ws);
     XRegion X;
     X.slots = (uint64_t*)(ws + xchg_ws(c).slots);
     const int grid = std::max(kClearWorkgroups, std::min(j.items, 1024));
     auto fn = c.dtype == TSB_BF16 ? (j.vec ? chain_rows<TSB_BF16, true> : chain_rows<TSB_BF16, false>)
                                   : (j.vec ? chain_rows<TSB_F32, true> : chain_rows<TSB_F32, false>);
-    fn<<<grid, kChainThreads, 0, st>>>(j, X, c.R, invT);
+    fn<<<grid + record_blocks(rec, kChainThreads), kChainThreads, 0, st>>>(j, X, c.R, invT, grid, rec);
     return hipGetLastError();
 }
+
+// LDS of a walk workgroup's slice (one recomputed in every pass needs none),
+// and what capacity is asked with: the largest a launch may need.
+static size_t walk_lds(const tsb_config& c, int G) {
+    const int span = walk_span(c.V, G);
+    return span <= kWalkHeldTokens ? (size_t)span * 2 * sizeof(double) : 0;
+}
+constexpr size_t kWalkLdsMax = (size_t)kWalkHeldTokens * 2 * sizeof(double);
+constexpr size_t trav_stack_bytes(int D) { return (size_t)(D + 1) * sizeof(TravState); }
 
 // Walk arguments shared by both walks.
 static WalkArgs walk_args(const tsb_config& c, float invT, const void* draft, const double* draft_lse,
@@ -1768,7 +1743,7 @@ static WalkArgs walk_args(const tsb_config& c, float invT, const void* draft, co
     A.pool_tok = nullptr;
     A.trans = nullptr;
     A.P = 0;
-    A.nrec = nullptr;
+    A.nrec = (const uint32_t*)(ws + w.nrec);
     A.reads_rows = 0;
     const XchgWs x = xchg_ws(c);
     A.cm = (const float*)(ws + x.cm);
@@ -1796,26 +1771,27 @@ hipError_t launch_verify(const tsb_config& c, float invT, const void* draft, con
     // streamed only for the optional normaliser output
     const bool reads = walk_reads_rows(c);
     if (stages & kStageTarget) {
-        if ((out.target_lse || !reads) && (e = launch_target_partials(c, invT, target, tree, w, ws, st)) != hipSuccess)
+        const RecordJob rec{draft, target, tree, node_tok, draft_lse, (uint32_t*)(ws + w.nrec), c.R, c.B, c.D, c.V};
+        const RecordJob none{};
+        if ((out.target_lse || !reads) &&
+            (e = launch_target_partials(c, invT, target, tree, w, ws, st, reads ? none : rec)) != hipSuccess)
             return e;
-        if (reads && (e = launch_chain_rows(c, invT, target, ws, st)) != hipSuccess) return e;
+        if (reads && (e = launch_chain_rows(c, invT, target, ws, st, rec)) != hipSuccess) return e;
     }
     if (!(stages & kStageWalk)) return hipSuccess;
     WalkArgs A = walk_args(c, invT, draft, draft_lse, target, tree, node_tok, step, out, w, ws);
     A.reads_rows = reads ? 1 : 0;
-    if (stages & kWalkRecords) A.nrec = (const uint32_t*)(ws + w.nrec);
     const bool vec4 = c.V % 4 == 0 && ((uintptr_t)target & 15) == 0 && ((uintptr_t)draft & 15) == 0;
-    const void* fn = nullptr;
-    if (c.dtype == TSB_BF16)
-        fn = vec4 ? (const void*)verify_walk<TSB_BF16, true> : (const void*)verify_walk<TSB_BF16, false>;
-    else
-        fn = vec4 ? (const void*)verify_walk<TSB_F32, true> : (const void*)verify_walk<TSB_F32, false>;
-    const size_t lds = 2 * (size_t)kWalkCache * sizeof(double);
+    const bool bf16 = c.dtype == TSB_BF16;
+    const void* fn = bf16 ? (vec4 ? (const void*)verify_walk<TSB_BF16, true> : (const void*)verify_walk<TSB_BF16, false>)
+                          : (vec4 ? (const void*)verify_walk<TSB_F32, true> : (const void*)verify_walk<TSB_F32, false>);
+    const int G = geometry(c).G;
+    const size_t lds = walk_lds(c, G);
     int cap = 0;
-    if ((e = walk_capacity(fn, 0, c.dtype == TSB_BF16 ? 1 : 0, vec4 ? 1 : 0, lds, &cap)) != hipSuccess) return e;
+    if ((e = walk_capacity(fn, 0, bf16 ? 1 : 0, vec4 ? 1 : 0, kWalkLdsMax, &cap)) != hipSuccess) return e;
     if (cap < 1) return hipErrorLaunchOutOfResources;
     if ((e = hook_before(TSB_KERNEL_VERIFY_WALK, st)) != hipSuccess) return e;
-    if ((e = launch_walk_grid(fn, A, c.R, geometry(c).G, cap, lds, st)) != hipSuccess) return e;
+    if ((e = launch_walk_grid(fn, A, c.R, G, cap, lds, st)) != hipSuccess) return e;
     return hook_after(TSB_KERNEL_VERIFY_WALK, st);
 }
 
@@ -1824,22 +1800,22 @@ hipError_t launch_verify_traversal(const tsb_config& c, float invT, const void* 
                                    const tsb_verdict& out, char* ws, hipStream_t st, int stages) {
     const VerifyWs w = verify_ws(c);
     hipError_t e = hipSuccess;
-    if ((stages & kStageTarget) && (e = launch_target_partials(c, invT, target, tree, w, ws, st)) != hipSuccess)
+    const RecordJob rec{draft, target, tree, node_tok, draft_lse, (uint32_t*)(ws + w.nrec), c.R, c.B, c.D, c.V};
+    if ((stages & kStageTarget) && (e = launch_target_partials(c, invT, target, tree, w, ws, st, rec)) != hipSuccess)
         return e;
     if (!(stages & kStageWalk)) return hipSuccess;
     WalkArgs A = walk_args(c, invT, draft, draft_lse, target, tree, node_tok, step, out, w, ws);
     const bool vec4 = c.V % 4 == 0 && ((uintptr_t)target & 15) == 0 && ((uintptr_t)draft & 15) == 0;
-    const void* fn = nullptr;
-    if (c.dtype == TSB_BF16)
-        fn = vec4 ? (const void*)verify_traversal<TSB_BF16, true> : (const void*)verify_traversal<TSB_BF16, false>;
-    else
-        fn = vec4 ? (const void*)verify_traversal<TSB_F32, true> : (const void*)verify_traversal<TSB_F32, false>;
-    const size_t lds = 2 * (size_t)kWalkCache * sizeof(double);
+    const bool bf16 = c.dtype == TSB_BF16;
+    const void* fn = bf16 ? (vec4 ? (const void*)verify_traversal<TSB_BF16, true> : (const void*)verify_traversal<TSB_BF16, false>)
+                          : (vec4 ? (const void*)verify_traversal<TSB_F32, true> : (const void*)verify_traversal<TSB_F32, false>);
+    const int G = geometry(c).G;
+    const size_t lds = walk_lds(c, G) + trav_stack_bytes(c.D);
     int cap = 0;
-    if ((e = walk_capacity(fn, 2, c.dtype == TSB_BF16 ? 1 : 0, vec4 ? 1 : 0, lds, &cap)) != hipSuccess) return e;
+    if ((e = walk_capacity(fn, 2, bf16 ? 1 : 0, vec4 ? 1 : 0, kWalkLdsMax + trav_stack_bytes(TSB_MAX_D), &cap)) != hipSuccess) return e;
     if (cap < 1) return hipErrorLaunchOutOfResources;
     if ((e = hook_before(TSB_KERNEL_TRAVERSAL_WALK, st)) != hipSuccess) return e;
-    if ((e = launch_walk_grid(fn, A, c.R, geometry(c).G, cap, lds, st)) != hipSuccess) return e;
+    if ((e = launch_walk_grid(fn, A, c.R, G, cap, lds, st)) != hipSuccess) return e;
     return hook_after(TSB_KERNEL_TRAVERSAL_WALK, st);
 }
 
@@ -1849,7 +1825,8 @@ hipError_t launch_pool_verify(const tsb_config& c, int P, float invT, const void
                               hipStream_t st, int stages) {
     const VerifyWs w = pool_verify_ws(c);
     hipError_t e = hipSuccess;
-    if ((stages & kStageTarget) && (e = launch_target_partials(c, invT, target, tree, w, ws, st)) != hipSuccess)
+    if ((stages & kStageTarget) &&
+        (e = launch_target_partials(c, invT, target, tree, w, ws, st, RecordJob{})) != hipSuccess)
         return e;
     if (!(stages & kStageWalk)) return hipSuccess;
     WalkArgs A = walk_args(c, invT, draft, nullptr, target, tree, node_tok, step, out, w, ws);

@@ -116,6 +116,37 @@ __device__ __forceinline__ double exp64(double x, const double* t) {
     return ldexp(fma(s, p, s), m);
 }
 
+// As exp64 with ln2/256 in two parts, so that the reduction's error stays
+// below 1e-19 over the whole range (scalars, where the library's exp would
+// keep its constants in registers over a whole kernel).
+__device__ __forceinline__ double exp64x(double x, const double* t) {
+    constexpr double kInvL = 369.3299304675746;            // 256 / ln2
+    constexpr double kL = 0.0027076061740622863;           // fl64(ln2) / 256
+    constexpr double kLlo = 2.3190468138462996e-17 / 256;  // (ln2 - fl64(ln2)) / 256
+    x = fmax(x, -746.0);                                   // e^-746 rounds to 0
+    const double n = rint(x * kInvL);
+    const double r = fma(-n, kLlo, fma(-n, kL, x));
+    const int ni = (int)n;
+    const int j = ni & (kExpTable - 1);
+    const int m = ni >> 8;
+    double p = fma(r, 1.0 / 24.0, 1.0 / 6.0);
+    p = fma(r, p, 0.5);
+    p = fma(r, p, 1.0);
+    p = p * r;
+    const double s = t[j];
+    return ldexp(fma(s, p, s), m);
+}
+
+// ln x for a positive x in binary32's normal range: a binary32 estimate y and
+// one step of the exponential, ln x = y + ln(1 + d) with d = x e^-y - 1 below
+// 1e-6 (its series to the third power; the error is the exponential's, about
+// 2e-16 absolute).
+__device__ __forceinline__ double log64(double x, const double* t) {
+    const double y = (double)(__log2f((float)x) * 0.69314718055994531f);
+    const double d = fma(x, exp64x(-y, t), -1.0);
+    return y + fma(d * d, fma(d, 1.0 / 3.0, -0.5), d);
+}
+
 // ---------------------------------------------------------------- logits
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -297,6 +328,29 @@ __device__ __forceinline__ uint64_t lane_u64(uint64_t v, int l) {
 }
 __device__ __forceinline__ double lane_f64(double v, int l) {
     return __longlong_as_double((long long)lane_u64((uint64_t)__double_as_longlong(v), l));
+}
+
+// One step of a wave maximum through DPP: lanes of the rows in ROWMASK take
+// the larger of their key and the key DPP control CTRL moves to them.
+template <int CTRL, int ROWMASK>
+__device__ __forceinline__ uint64_t dpp_max_step(uint64_t v) {
+    const int h = (int)(uint32_t)(v >> 32), l = (int)(uint32_t)v;
+    const uint32_t oh = (uint32_t)__builtin_amdgcn_update_dpp(h, h, CTRL, ROWMASK, 0xf, false);
+    const uint32_t ol = (uint32_t)__builtin_amdgcn_update_dpp(l, l, CTRL, ROWMASK, 0xf, false);
+    const uint64_t o = ((uint64_t)oh << 32) | ol;
+    return o > v ? o : v;
+}
+
+// Wave-uniform maximum of a uint64 key: within quads, half rows and rows by
+// DPP permutations, then row broadcasts carry the running maximum to lane 63.
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
+    v = dpp_max_step<0xB1, 0xF>(v);   // quad_perm [1, 0, 3, 2]
+    v = dpp_max_step<0x4E, 0xF>(v);   // quad_perm [2, 3, 0, 1]
+    v = dpp_max_step<0x141, 0xF>(v);  // row_half_mirror
+    v = dpp_max_step<0x140, 0xF>(v);  // row_mirror
+    v = dpp_max_step<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_max_step<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return lane_u64(v, kWave - 1);
 }
 
 // ---------------------------------------------------------------- walk support

@@ -5,6 +5,10 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
+#include <hip/hip_runtime.h>
+
 #include "../../include/tsubame.h"
 
 namespace tsb {
@@ -15,7 +19,12 @@ enum : uint32_t { kStreamReplay = 0, kStreamAccept = 1, kStreamBonus = 2 };
 constexpr int kBlock = 256;          // threads per workgroup of the streaming kernels
 constexpr int kReplayTile = 4096;    // vocabulary tile of the replay scan
 constexpr int kWalkGroupsMax = 128;  // workgroups per request in verification
-constexpr int kWalkTokensPerGroup = 9728;  // tokens whose binary64 (p, q) one walk workgroup holds in LDS
+constexpr int kWalkThreadsPerGroup = 512;
+// Tokens whose binary64 (p, q) a walk workgroup holds in LDS: up to
+// kWalkSliceTokens with another workgroup beside it on the compute unit (77 KB
+// of its 160 each), kWalkHeldTokens at most.
+constexpr int kWalkSliceTokens = 4800, kWalkHeldTokens = 9472;
+constexpr int kWalkResident = 512;      // walk workgroups two to a compute unit
 constexpr int kTargetWorkgroups = 2048;  // target stream: 8 resident workgroups on each of 256 CUs
 constexpr int kClearWorkgroups = 64;      // a target job without rows: workgroups that clear the exchange slots
 // A walk that reads the target rows it enters takes the rows of nodes 0 and
@@ -37,6 +46,9 @@ constexpr long long kStreamRowsBytes = 128ll << 20;
 constexpr int kTargetMinChunk = 32768;
 constexpr int kDraftWorkgroups = 512;    // row statistics: two 512-thread workgroups on each of 256 CUs
 constexpr int kDraftMinSeg = 16384;      // shortest draft segment (elements), unless the row is shorter
+
+// Tokens of a walk workgroup's slice (a multiple of 4; the last may be shorter).
+__host__ __device__ inline int walk_span(int V, int G) { return ((V + G - 1) / G + 3) & ~3; }
 
 struct Geometry {
     int S1;          // workgroups per draft row (row statistics)
@@ -79,12 +91,17 @@ inline Geometry geometry(const tsb_config& c) {
     g.G4 = (int)((n4 + g.chunk4 - 1) / g.chunk4);
     g.S4 = (int)((c.V - 1) / g.chunk4) + 2;
     g.T = ceil_div(c.V, kReplayTile);
-    // walk: about one workgroup per compute unit over the batch, and enough
-    // per request that a slice fits the LDS cache
-    int gw = 256 / (c.R > 0 ? c.R : 1);
-    const int gmin = ceil_div(c.V, kWalkTokensPerGroup);
-    if (gw < gmin) gw = gmin;
-    g.G = gw < 1 ? 1 : (gw > kWalkGroupsMax ? kWalkGroupsMax : gw);
+    // walk: at least the workgroups per request whose slices leave room for
+    // another workgroup beside them, and while all requests' run at once, up to
+    // one per 2048 tokens among up to 32, or one per 4096 (an exchange costs
+    // 1.3 us among 16 workgroups, 1.7 among 32, 2.1 among 64, 3.4 among 128: a
+    // walk over 8 x 151936 tokens took 50 us with 38, 54 with 64 and 55 with 17;
+    // over 3 x 50001 29 with 25, 32 with 13 and 38 with 6). One workgroup, which
+    // exchanges nothing, up to 4096 tokens.
+    const int gmin = ceil_div(c.V, kWalkSliceTokens);
+    const int gmax = c.V <= 4096 ? 1 : std::min(ceil_div(c.V, 2048), std::max(32, ceil_div(c.V, 4096)));
+    const int gw = std::max(gmin, std::min(gmax, kWalkResident / c.R));
+    g.G = gw > kWalkGroupsMax ? kWalkGroupsMax : gw;
     return g;
 }
 

@@ -96,10 +96,10 @@ hipError_t launch_replay(const tsb_config& c, float invT, const void* draft, con
 // Verification is two stages: the target stream (row normaliser partials of
 // every row of the tree, for the optional normaliser output, and for the
 // verifiers that need every row), or else the clearing of the exchange
-// slots, and the walk. A round runs the target stage in the replay scan's
-// grid, its merge writes the node records, and then the walk runs alone,
-// reading them (kWalkRecords).
-enum : int { kStageTarget = 1, kStageWalk = 2, kStagesAll = 3, kWalkRecords = 4 };
+// slots, with the walk's node records, and the walk. A round runs the target
+// stage in the replay scan's grid, its merge writes the node records, and
+// then the walk runs alone.
+enum : int { kStageTarget = 1, kStageWalk = 2, kStagesAll = 3 };
 
 hipError_t launch_verify(const tsb_config& c, float invT, const void* draft, const double* draft_lse,
                          const void* target, const tsb_tree& tree, const int32_t* node_tok, uint32_t step,

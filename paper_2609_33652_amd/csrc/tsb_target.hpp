@@ -267,17 +267,104 @@ __device__ __forceinline__ double target_row_lse(const float* __restrict__ tm, c
     return (double)M + log(tot);
 }
 
-// Node records for the walk, written by the replay merge of a whole round:
-// everything the walk reads when it enters node u, in one record of
-// kRecWords 32-bit words, so that entering a node costs one memory round
-// trip (besides its target row, when the walk reads rows as it enters their
-// nodes). Words: 0 m (children; 0 for a leaf), 1 first child, 2 depth,
-// 3 flags (kRecOk: the node passed the topology checks; kRecTargetBad: its
-// target row is unusable), 4-5 the row's streamed normaliser L0 (binary64;
-// both only when every row was streamed before the merge, else 0), 6-7 the
-// draft normaliser of the children's row, then per child j (up to
-// TSB_MAX_K) four words at 8 + 4 j: token, draft logit x invT and target
-// logit x invT (binary32 bits; 0 for a token outside [0, V)), unused.
-constexpr uint32_t kRecOk = 1u, kRecTargetBad = 2u;
+// Whether a target row held a non-finite logit (or none finite).
+__device__ __forceinline__ bool target_row_bad(const float* __restrict__ tm, const int* __restrict__ tf, int P,
+                                               size_t row) {
+    const size_t o = row * (size_t)P;
+    float M = -INFINITY;
+    int b = 0;
+    for (int s = 0; s < P; ++s) {
+        M = fmaxf(M, tm[o + s]);
+        b |= tf[o + s];
+    }
+    return b || M == -INFINITY;
+}
+
+// Node records for the walks, written by the replay merge of a whole round
+// and by the kernel before a walk launched on its own: everything a walk reads
+// when it enters node u, in one record of kRecWords 32-bit words, so that
+// entering a node costs one memory round trip (besides its target row, when
+// the walk reads rows as it enters their nodes). Words: 0 m (children; 0 for a
+// leaf), 1 first child, 2 depth, 3 flags (kRecOk: the node passed the topology
+// checks; kRecTargetBad: its target row is unusable; kRecNoL0: neither that nor
+// the normaliser was known when the record was written), 4-5 the row's
+// streamed normaliser L0 (binary64), 6-7 the draft normaliser of the
+// children's row, then per child j (up to TSB_MAX_K) four words at 8 + 4 j:
+// token, draft logit x invT and target logit x invT (binary32 bits; 0 for a
+// token outside [0, V)), and the child's own n_children as given.
+constexpr uint32_t kRecOk = 1u, kRecTargetBad = 2u, kRecNoL0 = 4u;
+
+// The parts that do not depend on the children's tokens (lane j: child j's).
+struct NodeHead {
+    TreeNode t;
+    double L0, Ld;
+    int bad, kids;
+    bool l0;
+};
+__device__ __forceinline__ NodeHead node_head(const tsb_tree& tree, const double* __restrict__ draft_lse, int r,
+                                              int u, int n, size_t tb, int D, int lane) {
+    NodeHead h;
+    h.t = tree_node(tree, tb, u, n, D);
+    h.L0 = 0.0;
+    h.bad = 0;
+    h.l0 = false;
+    const int m = h.t.ok ? h.t.m : 0;
+    h.kids = lane < m ? tree.n_children[tb + h.t.fc + lane] : 0;
+    h.Ld = m > 0 ? draft_lse[(size_t)r * D + h.t.d] : 0.0;
+    return h;
+}
+
+// The record of flat node `node` (request r) by one wave; tok: child lane's token.
+template <int DT>
+__device__ __forceinline__ void write_record(uint32_t* __restrict__ nrec, const NodeHead& h,
+                                             const void* __restrict__ draft, const void* __restrict__ target, int V,
+                                             int D, float invT, int r, size_t node, int tok, int lane) {
+    const TreeNode& t = h.t;
+    uint32_t* rp = nrec + node * kRecWords;
+    const int m = t.ok ? t.m : 0;
+    if (lane == 0) {
+        const uint64_t l0 = (uint64_t)__double_as_longlong(h.L0), ld = (uint64_t)__double_as_longlong(h.Ld);
+        *(uint4*)rp = make_uint4((uint32_t)m, (uint32_t)t.fc, (uint32_t)t.d,
+                                 (t.ok ? kRecOk : 0u) | (h.bad ? kRecTargetBad : 0u) | (h.l0 ? 0u : kRecNoL0));
+        *(uint4*)(rp + 4) = make_uint4((uint32_t)l0, (uint32_t)(l0 >> 32), (uint32_t)ld, (uint32_t)(ld >> 32));
+    }
+    if (lane < m) {
+        const size_t trow = node * (size_t)V;
+        const size_t drow = ((size_t)r * D + t.d) * (size_t)V;
+        const bool yok = tok >= 0 && tok < V;
+        const float xd = yok ? load_logit<DT>(draft, drow + tok) * invT : 0.f;
+        const float xt = yok ? load_logit<DT>(target, trow + tok) * invT : 0.f;
+        *(uint4*)(rp + 8 + 4 * lane) = make_uint4((uint32_t)tok, __float_as_uint(xd), __float_as_uint(xt), (uint32_t)h.kids);
+    }
+}
+
+// The records of a walk launched on its own, a wave per node, on workgroups
+// after those of the kernel before it (nrec null: none).
+struct RecordJob {
+    const void* draft;
+    const void* target;
+    tsb_tree tree;
+    const int32_t* node_tok;
+    const double* draft_lse;
+    uint32_t* nrec;
+    int R, B, D, V;
+};
+inline int record_blocks(const RecordJob& j, int threads) {
+    return j.nrec ? (j.R * (j.B + 1) + threads / kWave - 1) / (threads / kWave) : 0;
+}
+template <int DT>
+__device__ __forceinline__ void record_block(const RecordJob& j, int block, float invT) {
+    const int lane = threadIdx.x % kWave;
+    const int node = block * (int)(blockDim.x / kWave) + (int)(threadIdx.x / kWave);
+    if (node >= j.R * (j.B + 1)) return;
+    const int r = node / (j.B + 1), u = node % (j.B + 1);
+    const size_t tb = (size_t)r * (j.B + 1);
+    const int nn = j.tree.n_nodes[r];
+    const int n = tree_count_ok(nn, j.B) ? nn : 0;
+    if (u >= n) return;
+    const NodeHead h = node_head(j.tree, j.draft_lse, r, u, n, tb, j.D, lane);
+    const int tok = h.t.ok && lane < h.t.m ? j.node_tok[tb + h.t.fc + lane] : -1;
+    write_record<DT>(j.nrec, h, j.draft, j.target, j.V, j.D, invT, r, tb + u, tok, lane);
+}
 
 }  // namespace tsb

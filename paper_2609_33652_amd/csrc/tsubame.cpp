@@ -254,7 +254,7 @@ tsb_status step_round(const tsb_config* cfg, const void* draft, const void* targ
     hipError_t e = tsb::launch_plan(*cfg, invT, draft, draft_lse, topk_tok, topk_lp, *tree, out->req_status, ws, stream,
                                     0, traversal ? nullptr : &cj);
     if (e != hipSuccess) return hip_fail(e, (snprintf(where, sizeof where, "%s/plan", name), where));
-    const tsb::TargetJob tj = tsb::target_job(*cfg, target, *tree, traversal ? nullptr : draft_lse, ws,
+    const tsb::TargetJob tj = tsb::target_job(*cfg, target, *tree, draft_lse, ws,
                                               traversal || out->target_lse != nullptr ||
                                                   !tsb::walk_reads_rows(*cfg));
     e = tsb::launch_replay(*cfg, invT, draft, topk_tok, *tree, step, node_tok, ws, stream, &tj);
@@ -262,7 +262,7 @@ tsb_status step_round(const tsb_config* cfg, const void* draft, const void* targ
     e = traversal ? tsb::launch_verify_traversal(*cfg, invT, draft, draft_lse, target, *tree, node_tok, step, *out, ws,
                                                  stream, tsb::kStageWalk)
                   : tsb::launch_verify(*cfg, invT, draft, draft_lse, target, *tree, node_tok, step, *out, ws, stream,
-                                       tsb::kStageWalk | tsb::kWalkRecords);
+                                       tsb::kStageWalk);
     if (e != hipSuccess) return hip_fail(e, (snprintf(where, sizeof where, "%s/walk", name), where));
     return TSB_OK;
 }
