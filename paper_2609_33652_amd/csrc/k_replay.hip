@@ -4,8 +4,8 @@
 // (Gumbel-top-k = ordered sampling without replacement).
 //
 //   replay_threshold  one wave per parent: a lower bound of its m-th key
-//                 from its planning candidates and a sample of the row; one
-//                 more workgroup writes
+//                 from its planning candidates and a sample of the row; a
+//                 workgroup per 2048 nodes writes
 //                 the flat list of the parents of the batch (request-major,
 //                 BFS order, so a depth's parents are contiguous).
 //   replay_scan   one wave per (parent, vocabulary tile) item, dealt
@@ -63,61 +63,82 @@ __device__ __forceinline__ bool replay_parent(const tsb_tree& tree, int r, int u
     return nd->ok && nd->m > 0 && nd->m <= K;
 }
 
+// Nodes of the parent list that one workgroup writes. A workgroup counts the
+// parents before its own nodes itself instead of waiting for the others: a
+// chunk counted is a chunk of loads (all in flight together), a chunk written
+// by the same workgroup before was a serial step of 4 us (16448 nodes: the
+// launch 39.1 us with one workgroup, 20.4 with nine; 2064 nodes: 10.3 either
+// way, the thresholds' own time).
+constexpr int kListPer = 8;
+constexpr int kListNodes = kBlock * kListPer;
+
+// Which of nodes i0 + k * 64 + lane (k < kListPer) are parents: bit `lane` of
+// par[k]. Every entry is loaded before any is tested (replay_parent's
+// conditions, without its dependent loads).
+__device__ __forceinline__ void list_parents(int i0, int total_nodes, int B, int D, int K, const tsb_tree& tree,
+                                             uint64_t (&par)[kListPer]) {
+    const int lane = lane_id();
+    int nn[kListPer], nm[kListPer], nfc[kListPer], nd[kListPer];
+#pragma unroll
+    for (int k = 0; k < kListPer; ++k) {
+        const int i = i0 + k * kWave + lane;
+        const size_t e = i < total_nodes ? (size_t)i : 0;
+        nn[k] = tree.n_nodes[e / (size_t)(B + 1)];
+        nm[k] = tree.n_children[e];
+        nfc[k] = tree.first_child[e];
+        nd[k] = tree.depth[e];
+    }
+#pragma unroll
+    for (int k = 0; k < kListPer; ++k) {
+        const int i = i0 + k * kWave + lane;
+        const int u = i % (B + 1);
+        const int n = tree_count_ok(nn[k], B) ? nn[k] : 0;
+        const int m = nm[k], fc = nfc[k], d = nd[k];
+        const bool ok = m > 0 && m <= TSB_MAX_K && fc > u && fc <= n - m && d >= 0 && d < D;
+        par[k] = __ballot(i < total_nodes && u < n && ok && m <= K);
+    }
+}
+
 // Flat list of every parent, request-major, BFS order within a request (so
 // parents of one (request, depth) are contiguous): plist[i] =
-// r * (B + 1) + u; ptotal[0] = list length. One workgroup of kBlock threads:
-// a thread takes eight consecutive nodes of a chunk (their loads in flight
-// together) and a block scan places them.
-__device__ void prep_list(int R, int B, int D, int K, const tsb_tree& tree, int* __restrict__ plist,
-                          int* __restrict__ ptotal) {
-    constexpr int kPer = 8;
-    __shared__ int s_w[kBlock / kWave];
-    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+// r * (B + 1) + u; ptotal[0] = list length. Workgroup `chunk` of `chunks`
+// writes the parents of its kListNodes nodes (a wave kListPer * 64 of them).
+__device__ void prep_list(int chunk, int chunks, int R, int B, int D, int K, const tsb_tree& tree,
+                          int* __restrict__ plist, int* __restrict__ ptotal) {
+    __shared__ int s_before[kBlock / kWave], s_own[kBlock / kWave];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const int total_nodes = R * (B + 1);
-    int out = 0;
-    for (int c0 = 0; c0 < total_nodes; c0 += kBlock * kPer) {
-        // every entry of the thread's nodes is loaded before any is tested
-        // (replay_parent's conditions, without its dependent loads)
-        int nn[kPer], nm[kPer], nfc[kPer], nd[kPer];
+    uint64_t par[kListPer];
+    int before = 0;
+    for (int c = 0; c < chunk; ++c) {
+        list_parents(c * kListNodes + wave * kListPer * kWave, total_nodes, B, D, K, tree, par);
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int i = c0 + tid * kPer + k;
-            const bool in = i < total_nodes;
-            const int r = in ? i / (B + 1) : 0;
-            const size_t e = in ? (size_t)i : 0;
-            nn[k] = in ? tree.n_nodes[r] : 0;
-            nm[k] = tree.n_children[e];
-            nfc[k] = tree.first_child[e];
-            nd[k] = tree.depth[e];
-        }
-        int flags = 0;  // bit k: node c0 + tid * kPer + k has children
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            const int i = c0 + tid * kPer + k;
-            const int u = i % (B + 1);
-            const int n = tree_count_ok(nn[k], B) ? nn[k] : 0;
-            const int m = nm[k], fc = nfc[k], d = nd[k];
-            const bool ok = m == 0 || (m > 0 && m <= TSB_MAX_K && fc > u && fc <= n - m && d >= 0 && d < D);
-            if (i < total_nodes && u < n && ok && m > 0 && m <= K) flags |= 1 << k;
-        }
-        int wt;
-        const int off = wave_excl_scan<4>(__popc(flags), wt);
-        if (lane == 0) s_w[wave] = wt;
-        __syncthreads();
-        int o = out, tot = 0;
-        for (int w = 0; w < kBlock / kWave; ++w) {
-            const int x = s_w[w];
-            o += w < wave ? x : 0;
-            tot += x;
-        }
-        o += off;
-#pragma unroll
-        for (int k = 0; k < kPer; ++k)
-            if ((flags >> k) & 1) plist[o++] = c0 + tid * kPer + k;
-        out += tot;
-        __syncthreads();  // s_w is rewritten by the next chunk
+        for (int k = 0; k < kListPer; ++k) before += __popcll(par[k]);
     }
-    if (tid == 0) ptotal[0] = out;
+    const int i0 = chunk * kListNodes + wave * kListPer * kWave;
+    list_parents(i0, total_nodes, B, D, K, tree, par);
+    int own = 0;
+#pragma unroll
+    for (int k = 0; k < kListPer; ++k) own += __popcll(par[k]);
+    if (lane == 0) {
+        s_before[wave] = before;
+        s_own[wave] = own;
+    }
+    __syncthreads();
+    int o = 0, end = 0;
+    for (int w = 0; w < kBlock / kWave; ++w) {
+        o += s_before[w] + (w < wave ? s_own[w] : 0);
+        end += s_before[w] + s_own[w];
+    }
+#pragma unroll
+    for (int k = 0; k < kListPer; ++k) {
+        if ((par[k] >> lane) & 1)
+            plist[o + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(par[k] >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)par[k], 0u))] =
+                i0 + k * kWave + lane;
+        o += __popcll(par[k]);
+    }
+    if (chunk == chunks - 1 && threadIdx.x == 0) ptotal[0] = end;
 }
 
 __device__ __forceinline__ bool key_better(float ka, int ia, float kb, int ib) {
@@ -212,7 +233,7 @@ struct SampleGroups {
 // flat ones (there the candidates alone let 75 to 240 tokens of a tile pass
 // for 6 to 10 children, each inserted one by one, and such items ended the
 // scan). It is stored with what the scan needs of the parent in one record
-// (c_d, thr, depth, m_u). The grid's last workgroup builds the parent list
+// (c_d, thr, depth, m_u). The grid's first workgroups build the parent list
 // instead.
 template <int DT>
 __global__ __launch_bounds__(kBlock) void replay_threshold(const void* __restrict__ draft, int R, int V, int D, int B,
@@ -220,12 +241,13 @@ __global__ __launch_bounds__(kBlock) void replay_threshold(const void* __restric
                                                            tsb_tree tree, uint32_t k0, uint32_t k1, uint32_t step,
                                                            int prune, int vec, float4* __restrict__ rec,
                                                            int* __restrict__ plist, int* __restrict__ ptotal) {
-    if (blockIdx.x == gridDim.x - 1) {
-        prep_list(R, B, D, K, tree, plist, ptotal);
+    const int chunks = (R * (B + 1) + kListNodes - 1) / kListNodes;
+    if ((int)blockIdx.x < chunks) {
+        prep_list(blockIdx.x, chunks, R, B, D, K, tree, plist, ptotal);
         return;
     }
     const int lane = threadIdx.x % kWave;
-    const int node = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+    const int node = ((int)blockIdx.x - chunks) * (kBlock / kWave) + threadIdx.x / kWave;
     if (node >= R * (B + 1)) return;
     const int r = node / (B + 1), u = node % (B + 1);
     TreeNode nd;
@@ -875,8 +897,9 @@ hipError_t launch_replay(const tsb_config& c, float invT, const void* draft, con
     const int prune = (c.flags & TSB_FLAG_NO_PRUNE) ? 0 : 1;
     const bool vec = c.V % 4 == 0 && ((uintptr_t)draft & 15) == 0;
     float4* rec = (float4*)(ws + w.thr);
-    // one workgroup per four nodes, and one more for the parent list
-    const int nthr = (c.R * (c.B + 1) + kBlock / kWave - 1) / (kBlock / kWave) + 1;
+    // the parent list's workgroups, and one per four nodes
+    const int nodes = c.R * (c.B + 1);
+    const int nthr = (nodes + kListNodes - 1) / kListNodes + (nodes + kBlock / kWave - 1) / (kBlock / kWave);
     if (c.dtype == TSB_BF16)
         replay_threshold<TSB_BF16><<<nthr, kBlock, 0, st>>>(draft, c.R, c.V, c.D, c.B, c.K, invT, topk_tok, tree, k0,
                                                             k1, step, prune, vec ? 1 : 0, rec, plist, ptotal);
