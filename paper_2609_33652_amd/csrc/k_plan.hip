@@ -793,24 +793,32 @@ __global__ __launch_bounds__(kDraftThreads) __attribute__((amdgpu_waves_per_eu(4
 //    (depth, rank path) order. Path scores never increase from a node to its
 //    children or younger siblings (lp <= 0, sorted by rank), so the nodes
 //    scoring at least a threshold form a subtree that a level-by-level count
-//    enumerates. Each wave counts one candidate threshold per round:
+//    enumerates into a list. Eight waves first estimate the counts from
+//    histograms of path scores and count at thresholds around the estimated
+//    t*; a count in [B + 1, cap] lists every node scoring at least its
+//    threshold, and t* is selected among them. Otherwise each wave counts one
+//    candidate threshold per round:
 //      - hi: a threshold with count(hi) <= B, and m(hi), the largest node
 //        score below hi (count(m(hi)) > count(hi));
 //      - wave 0 counts at m(hi); if that reaches B + 1, t* = m(hi);
-//      - the other waves count at thresholds spread below m(hi); a count in
-//        [B + 1, cap] has every node scoring at least its threshold in LDS,
-//        and t* is selected among them;
+//      - the other waves count at thresholds spread below m(hi), one of which
+//        may land in [B + 1, cap];
 //      - otherwise hi moves to the lowest threshold that counted <= B (its
 //        count grows by at least one per round, so rounds end).
-// 3. Emission: one wave enumerates the admitted nodes level by level in
-//    (depth, rank path) order, which is the BFS canonical order: parents in
-//    order, children by rank. Chosen children form a prefix of each parent's
-//    children.
+// 3. Emission: the list is in (depth, rank path) order, which is the BFS
+//    canonical order (parents in order, children by rank), so the admitted
+//    nodes' indices are prefix sums over it. Chosen children form a prefix of
+//    each parent's children.
 constexpr int kPlanWaves = 16;
 constexpr int kPlanThreads = kPlanWaves * kWave;
 static_assert(kPlanThreads == kChainThreads, "the chain rows run on the planner's workgroups");
 constexpr int kChainGridMax = 1024;  // workgroups for the chain rows beside the planner
-constexpr int kPlanBuf = 12288;  // binary64 slots shared by the counting waves
+constexpr int kPlanBuf = 10240;  // listed nodes shared by the counting waves (binary64 score, 32-bit place)
+constexpr int kPlanCapMax = (5 * (TSB_MAX_B + 1) + 3) / 4;
+constexpr int kPlanSegs = (kPlanCapMax + kWave - 1) / kWave;
+constexpr int kHistWaves = 8;     // score histograms (one bin width each) for the first thresholds
+constexpr int kHistBins = kWave;  // a bin per lane
+constexpr int kGuessWaves = 8;    // thresholds around the guess (two waves a SIMD)
 
 struct PlanShared {
     float lp[TSB_MAX_D * TSB_MAX_K];
@@ -818,19 +826,20 @@ struct PlanShared {
     int bad;
     double piv[kPlanWaves];
     double mval[kPlanWaves];
+    double mins[kPlanWaves];
+    double guess[kHistWaves];
     int cnt[kPlanWaves];
     double tstar;
     int g;
+    int seg_gt[kPlanSegs], seg_eq[kPlanSegs];
+    int map[kPlanCapMax];  // per listed node: its selection counts, then its place in the tree
+    int nch[TSB_MAX_B + 1], fc[TSB_MAX_B + 1];
     union {
-        double buf[kPlanBuf];
         struct {
-            double score[TSB_MAX_B + 1];
-            int par[TSB_MAX_B + 1];
-            int rank[TSB_MAX_B + 1];
-            int depth[TSB_MAX_B + 1];
-            int nch[TSB_MAX_B + 1];
-            int fc[TSB_MAX_B + 1];
-        } t;
+            double score[kPlanBuf];
+            uint32_t node[kPlanBuf];  // (parent's list index + 1) << 16 | depth << 8 | rank
+        } b;
+        float hist[kHistWaves][2 * kHistBins];
     } u;
 };
 
@@ -854,25 +863,30 @@ __device__ void merge_row(SH& sh, int row, int rrow, int S, int K, float invT, c
                           int32_t* __restrict__ topk_tok, float* __restrict__ topk_lp) {
     const int lane = lane_id();
     const size_t o = (size_t)row * S;
-    float M = -INFINITY;
-    int bad = 0;
-    for (int s = lane; s < S; s += kWave) {
+    const int n = S * K;
+    // the first partials and keys of every lane are in flight together
+    const bool seg = lane < S;
+    const float m0 = seg ? pm[o + lane] : -INFINITY;
+    const double s0 = seg ? ps[o + lane] : 0.0;
+    int bad = seg ? pf[o + lane] : 0;
+    const uint64_t mine = lane < n ? pk[o * K + lane] : 0;
+    const uint64_t second = kWave + lane < n ? pk[o * K + kWave + lane] : 0;
+    float M = m0;
+    for (int s = kWave + lane; s < S; s += kWave) {
         M = fmaxf(M, pm[o + s]);
         bad |= pf[o + s];
     }
     M = wave_max(M);
     bad = wave_or(bad);
-    double tot = 0.0;
-    for (int s = lane; s < S; s += kWave)
+    double tot = m0 != -INFINITY ? s0 * exp((double)m0 - (double)M) : 0.0;
+    for (int s = kWave + lane; s < S; s += kWave)
         if (pm[o + s] != -INFINITY) tot += ps[o + s] * exp((double)pm[o + s] - (double)M);
     tot = wave_sum(tot);
 
-    const int n = S * K;
     uint64_t best;  // lane j < K: the j-th best candidate of the row
     if (n <= kWave) {
         // one candidate per lane: its rank is the number of larger keys (keys
         // are distinct, empty slots are 0); all lanes in parallel
-        const uint64_t mine = lane < n ? pk[o * K + lane] : 0;
         int rank = 0;
         for (int j = 0; j < n; ++j) rank += lane_u64(mine, j) > mine ? 1 : 0;
         __shared__ uint64_t s_rank[kPlanWaves][kWave];
@@ -882,10 +896,15 @@ __device__ void merge_row(SH& sh, int row, int rrow, int S, int K, float invT, c
         if (mine != 0 && rank < K) sr[rank] = mine;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         best = sr[lane];
+    } else if (n <= 2 * kWave) {
+        uint64_t v[2] = {mine, second};
+        wave_sort_desc<2>(v);
+        best = v[0];
     } else {
         WaveTopList top;
         top.init(K);
-        for (int base = 0; base < n; base += kWave) {
+        top.offer(mine, mine != 0);
+        for (int base = kWave; base < n; base += kWave) {
             const int i = base + lane;
             const uint64_t k = i < n ? pk[o * K + i] : 0;
             top.offer(k, i < n && k != 0);
@@ -903,7 +922,7 @@ __device__ void merge_row(SH& sh, int row, int rrow, int S, int K, float invT, c
         lp = a - l32;
         topk_tok[(size_t)row * K + lane] = (int32_t)cand_id(k);
         topk_lp[(size_t)row * K + lane] = lp;
-        sh.lp[rrow * K + lane] = lp;
+        sh.lp[rrow * K + lane] = lp;  // (past the finite prefix: -inf, or a row marked bad)
     }
     const int nfin = __popcll(__ballot(lane < K && lp > -INFINITY && lp < INFINITY));
     if (lane == 0) {
@@ -913,51 +932,107 @@ __device__ void merge_row(SH& sh, int row, int rrow, int S, int K, float invT, c
     }
 }
 
-// Number of nodes (root excluded) scoring at least tau, level by level, with
-// their scores stored in buf; cap + 1 once more than cap. m_out: the largest
-// node score below tau (-inf if none; meaningful without overflow). Lane l
-// takes candidate l % K of parent l / K, so a pass covers 64 / K parents and
-// one ballot compacts the children that reach tau in (parent, rank) order.
 __device__ __forceinline__ int lanes_below(uint64_t b) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
 }
 
-__device__ int plan_count(const PlanShared& sh, int Dp, int K, double tau, int cap, double* buf, double& m_out) {
+// Number of nodes (root excluded) scoring at least tau, listed level by level
+// in (parent, rank) order with their scores and places; cap + 1 once more than
+// cap. BELOW: m_out is the largest node score below tau (-inf if none;
+// meaningful without overflow). QUOTA: of the nodes scoring exactly tau only
+// the first `quota` are listed. Lane l takes candidate l % K of parent l / K,
+// so a pass covers 64 / K parents and one ballot compacts the children that
+// reach tau in (parent, rank) order. A pass is a serial step (LDS read,
+// compare, ballot, LDS write), so the next pass's scores and the next level's
+// candidates are read ahead of it; with four waves a SIMD it is bound by its
+// instructions (0.34 us a pass), which is why the loop's values are kept
+// uniform and the first round runs on half the waves without BELOW.
+template <bool QUOTA, bool BELOW>
+__device__ int plan_count(const PlanShared& sh, int Dp, int K, double tau, int cap, int quota, double* buf,
+                          uint32_t* node, double& m_out) {
     const int lane = lane_id();
     const int per = kWave / K;  // parents per pass
     const int pp = lane / K, pj = lane - pp * K;
     int total = 0;
-    int plo = 0, phi = 0;  // parents of the current level in buf; level 0: the root
+    int plo = 0, np = 1;  // parents of the current level in buf; level 0: the root
     double m = -INFINITY;
+    float lpn = pp < per ? sh.lp[pj] : -INFINITY;  // -inf in lanes without a candidate
     for (int k = 0; k < Dp; ++k) {
-        const int kk = sh.kfin[k];
-        const bool cand = pp < per && pj < kk;
-        const double lpj = cand ? (double)sh.lp[k * K + pj] : -INFINITY;
-        const int np = k == 0 ? 1 : phi - plo;
+        const double lpj = (double)lpn;
+        lpn = pp < per && k + 1 < Dp ? sh.lp[(k + 1) * K + pj] : -INFINITY;
         const int nstart = total;
-        for (int base = 0; base < np; base += per) {
+        const uint32_t place = (uint32_t)((k + 1) << 8 | pj);
+        double s = k > 0 && pp < np ? buf[plo + pp] : 0.0;
+        for (int base = 0; base < np && total <= cap; base += per) {
             const int i = base + pp;
-            const bool valid = cand && i < np;
-            const double s = (valid && k > 0) ? buf[plo + i] : 0.0;
             const double cs = s + lpj;
-            const bool ok = valid && cs >= tau;
-            if (valid && !ok) m = fmax(m, cs);  // children below tau (the best of them counts)
-            const uint64_t b = __ballot(ok);
-            const int cnt = __popcll(b);
-            if (total + cnt > cap) {
-                m_out = -INFINITY;
-                return cap + 1;
+            if (i + per < np) s = buf[plo + i + per];
+            bool ok = i < np && cs >= tau;  // tau is finite: never for -inf
+            if constexpr (QUOTA) {
+                const uint64_t be = __ballot(ok && cs == tau);
+                ok = ok && (cs > tau || lanes_below(be) < quota);
+                quota = __builtin_amdgcn_readfirstlane(quota - min(__popcll(be), quota));
             }
-            if (ok) buf[total + lanes_below(b)] = cs;
-            total += cnt;
+            if constexpr (BELOW)
+                if (i < np && !ok) m = fmax(m, cs);  // children below tau (the best of them counts)
+            const uint64_t b = __ballot(ok);
+            const int x = total + lanes_below(b);
+            if (ok && x < cap) {
+                buf[x] = cs;
+                node[x] = (k > 0 ? (uint32_t)(plo + i + 1) << 16 : 0u) | place;
+            }
+            total = __builtin_amdgcn_readfirstlane(total + __popcll(b));
         }
-        __threadfence_block();  // the next level reads these scores from other lanes
+        wave_lds_fence();  // the next level reads these scores from other lanes
         plo = nstart;
-        phi = total;
-        if (phi == plo) break;
+        np = __builtin_amdgcn_readfirstlane(total - nstart);
+        if (np == 0 || total > cap) break;
     }
-    m_out = wave_max_f64(m);
-    return total;
+    if constexpr (BELOW) m_out = wave_max_f64(total > cap ? -INFINITY : m);
+    return min(total, cap + 1);
+}
+
+// A threshold near which `want` nodes score at least that much, from a
+// histogram of path scores (bin b: scores near -b * width): level by level,
+// the sum over the candidates of the parents' histogram moved by the
+// candidate's rounded score. Lane b holds bin b; `h` is 64 zeros and the bins.
+// +inf when fewer than `want` paths fall into the bins.
+__device__ double plan_guess(const PlanShared& sh, int Dp, int K, float width, float want, float* h) {
+    const int lane = lane_id();
+    const float iw = 1.0f / width;
+    h[lane] = 0.f;
+    h[kHistBins + lane] = lane == 0 ? 1.f : 0.f;
+    wave_lds_fence();
+    float sum = 0.f;
+    float lpn = lane < K ? sh.lp[lane] : -INFINITY;
+    for (int k = 0; k < Dp; ++k) {
+        // bins to move by (64, out of range, for -inf; 0 for a candidate rounded above 0)
+        const int mv = (int)fminf((float)kHistBins, fmaxf(0.f, rintf(-lpn * iw)));
+        lpn = lane < K && k + 1 < Dp ? sh.lp[(k + 1) * K + lane] : -INFINITY;
+        // eight reads in flight (a loop of one read at a time waited for each:
+        // 10 us of the search); lanes past K read the zeros
+        float g = 0.f;
+        for (int j0 = 0; j0 < K; j0 += 8) {
+            float x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = h[kHistBins + lane - __builtin_amdgcn_readlane(mv, j0 + j)];
+            g += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+        }
+        if (__ballot(g > 0.f) == 0ull) break;
+        wave_lds_fence();
+        h[kHistBins + lane] = g;
+        sum += g;
+        wave_lds_fence();
+    }
+    // running sum over the bins
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const float t = __shfl_up(sum, o, kWave);
+        if (lane >= o) sum += t;
+    }
+    const uint64_t b = __ballot(sum >= want);
+    if (b == 0ull) return (double)INFINITY;
+    return -((double)(__ffsll((unsigned long long)b) - 1) + 0.5) * (double)width;
 }
 
 __global__ __launch_bounds__(kPlanThreads) void plan_tree(int D, int S, int K, int B, float invT,
@@ -985,45 +1060,100 @@ __global__ __launch_bounds__(kPlanThreads) void plan_tree(int D, int S, int K, i
     __shared__ PlanShared sh;
     const int r = blockIdx.x;
     const int tid = threadIdx.x;
-    const int wave = tid / kWave, lane = tid % kWave;
+    // values alike in a wave's lanes are kept in scalar registers (read from LDS
+    // or taken from the thread index they would make every loop over them a
+    // loop over execution masks)
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
     unsigned long long t_start = 0, t_merge = 0, t_search = 0;  // work counters (thread 0)
     int n_rounds = 0;
     if (stats && tid == 0) t_start = __builtin_amdgcn_s_memrealtime();
 
+    const int cap = (5 * (B + 1) + 3) / 4;
     if (tid == 0) sh.bad = 0;
+    for (int i = tid; i < cap; i += kPlanThreads) sh.map[i] = 0;
+    for (int i = tid; i < B + 1; i += kPlanThreads) {
+        sh.nch[i] = 0;
+        sh.fc[i] = 0x7FFFFFFF;
+    }
     __syncthreads();
     for (int d = wave; d < D; d += kPlanWaves)
         merge_row(sh, r * D + d, d, S, K, invT, pm, ps, pk, pf, draft_lse, topk_tok, topk_lp);
     __syncthreads();
     if (stats && tid == 0) t_merge = __builtin_amdgcn_s_memrealtime();
-    const bool nonfinite = sh.bad != 0;
+    const bool nonfinite = __builtin_amdgcn_readfirstlane(sh.bad) != 0;
     const int Dp = nonfinite ? 0 : D;
 
     // ---- threshold search (uniform control flow across the workgroup)
     // a count succeeds when it lands in [B + 1, cap]: a narrow window keeps
     // every count short (measured best at 1.25 (B + 1) over the workloads),
     // at the price of a round more now and then
-    const int cap = (5 * (B + 1) + 3) / 4;
     const int ns = min(kPlanWaves, kPlanBuf / cap);
-    double hi_m = (Dp > 0 && sh.kfin[0] > 0) ? (double)sh.lp[0] : -INFINITY;  // the best node's score
+    // the first thresholds: around the guess of the narrowest histogram that
+    // reaches past B + 1 nodes (bins double from wave to wave, so the threshold
+    // lies in the upper half of 64), half a bin apart: one of them lands in the
+    // window for all but a few trees in a hundred. Spread by powers of two
+    // below the best score, as they are without a guess, most needed a second
+    // round of counts. The launch, with one wave's emission replaced as well:
+    // 16 x 129 nodes, D = 16: 34.1 -> 24.3 us; 64 x 257, D = 32: 77.6 -> 41.0;
+    // one request of 65: 30.3 -> 20.3, of 17: 16.7 -> 12.2.
+    if (wave < kHistWaves && Dp > 0) {
+        const float width = 0.5f / (float)kHistBins * (float)(1 << wave);
+        const double t = plan_guess(sh, Dp, K, width, 1.12f * (float)(B + 1), sh.u.hist[wave]);
+        if (lane == 0) sh.guess[wave] = t;
+    }
+    __syncthreads();
+    double hi_m = lane_f64((Dp > 0 && sh.kfin[0] > 0) ? (double)sh.lp[0] : -INFINITY, 0);  // the best node's score
     int hi_cnt = 0;
     double lo = -INFINITY;
     int mode = 3;  // 1: t* = hi_m; 2: t* selected in a wave's buffer; 3: every node is chosen
     int src = -1;
+    const double gl = Dp > 0 && lane < kHistWaves ? sh.guess[lane] : INFINITY;
+    const uint64_t guessed = __ballot(gl < 0.0);
+    if (guessed) {
+        const int gw = __ffsll((unsigned long long)guessed) - 1;
+        const float gstep = 0.5f * (0.5f / (float)kHistBins) * (float)(1 << gw);
+        const int ng = min(ns, kGuessWaves);
+        if (wave < ng) {
+            const double tau = lane_f64(gl, gw) - (double)(gstep * ((float)wave - 0.5f * (float)(ng - 1)));
+            double unused;
+            const int c = plan_count<false, false>(sh, Dp, K, tau, cap, 0, sh.u.b.score + wave * cap,
+                                                   sh.u.b.node + wave * cap, unused);
+            if (lane == 0) {
+                sh.piv[wave] = tau;
+                sh.cnt[wave] = c;
+            }
+        }
+        __syncthreads();
+        n_rounds = 1;
+        const int cl = lane < ng ? sh.cnt[lane] : 0;
+        const double pl = lane < ng ? sh.piv[lane] : -INFINITY;
+        const uint64_t hit = __ballot(lane < ng && cl >= B + 1 && cl <= cap);
+        const uint64_t high = __ballot(lane < ng && cl > cap);
+        if (hit) {
+            mode = 2;
+            src = __ffsll((unsigned long long)hit) - 1;
+        } else if (high) {
+            lo = lane_f64(pl, __ffsll((unsigned long long)high) - 1);  // counts grow from wave to wave
+        }
+        __syncthreads();
+    }
     // every round raises count(hi) by at least one (at most B + 1 rounds); the
     // guard only bounds the loop
-    for (int round = 0; hi_m > -INFINITY; ++round) {
-        n_rounds = round + 1;
+    bool guard = false;
+    for (int round = 0; mode != 2 && hi_m > -INFINITY; ++round) {
+        ++n_rounds;
         if (round > B + 1) {
             mode = 1;
+            guard = true;
             break;
         }
         if (wave < ns) {
             const double tau = wave == 0 ? hi_m
-                               : (lo > -INFINITY ? hi_m - (hi_m - lo) * ((double)wave / (double)ns)
-                                                 : hi_m - 0.25 * exp2(0.5 * (double)(wave - 1)));
+                               : (lo > -INFINITY ? hi_m - (hi_m - lo) * (double)((float)wave / (float)ns)
+                                                 : hi_m - ldexp((wave & 1) ? 0.25 : 0.25 * M_SQRT2, (wave - 1) >> 1));
             double m;
-            const int c = plan_count(sh, Dp, K, tau, cap, sh.u.buf + wave * cap, m);
+            const int c = plan_count<false, true>(sh, Dp, K, tau, cap, 0, sh.u.b.score + wave * cap,
+                                                  sh.u.b.node + wave * cap, m);
             if (lane == 0) {
                 sh.piv[wave] = tau;
                 sh.cnt[wave] = c;
@@ -1031,142 +1161,170 @@ __global__ __launch_bounds__(kPlanThreads) void plan_tree(int D, int S, int K, i
             }
         }
         __syncthreads();
-        if (sh.cnt[0] >= B + 1) {
+        // lane w holds wave w's count; thresholds fall from wave 1 on, so the
+        // counts grow
+        const bool is_w = lane >= 1 && lane < ns;
+        const int cl = lane < ns ? sh.cnt[lane] : 0;
+        const double pl = lane < ns ? sh.piv[lane] : -INFINITY;
+        const double ml = lane < ns ? sh.mval[lane] : -INFINITY;
+        if (__builtin_amdgcn_readfirstlane(cl) >= B + 1) {
             mode = 1;
             break;
         }
-        int best = -1;
-        for (int w = 1; w < ns; ++w)
-            if (sh.cnt[w] >= B + 1 && sh.cnt[w] <= cap && (best < 0 || sh.piv[w] > sh.piv[best])) best = w;
-        if (best >= 0) {
+        const uint64_t hit = __ballot(is_w && cl >= B + 1 && cl <= cap);
+        if (hit) {
             mode = 2;
-            src = best;
+            src = __ffsll((unsigned long long)hit) - 1;
             break;
         }
-        int nh = 0;  // count(piv[0]) <= B here
-        double nlo = lo;
-        for (int w = 1; w < ns; ++w) {
-            if (sh.cnt[w] <= B && sh.piv[w] < sh.piv[nh]) nh = w;
-            if (sh.cnt[w] > cap && sh.piv[w] > nlo) nlo = sh.piv[w];
-        }
-        hi_cnt = sh.cnt[nh];
-        hi_m = sh.mval[nh];
-        lo = nlo;
+        // count(piv[0]) <= B here
+        const uint64_t low = __ballot(is_w && cl <= B && pl < lane_f64(pl, 0));
+        const uint64_t high = __ballot(is_w && cl > cap);
+        const int nh = low ? 63 - __clzll((long long)low) : 0;
+        hi_cnt = __builtin_amdgcn_readlane(cl, nh);
+        hi_m = lane_f64(ml, nh);
+        if (high) lo = fmax(lo, lane_f64(pl, __ffsll((unsigned long long)high) - 1));
+        src = nh;  // lists every node if nothing scores below
         __syncthreads();
     }
+    // t*, the number g of nodes above it, and a list that holds every node of
+    // the tree
+    double tstar = -INFINITY;  // mode 3: every node scores above it
+    int quota = 0;             // nodes scoring exactly t* still admitted
     if (mode == 1) {
-        if (tid == 0) {
-            sh.tstar = hi_m;
-            sh.g = hi_cnt;
+        tstar = hi_m;
+        quota = B - hi_cnt;
+        src = 0;
+        if (guard || __builtin_amdgcn_readfirstlane(sh.cnt[0]) > cap) {
+            // more nodes than a buffer holds score t*: list the admitted ones
+            __syncthreads();
+            if (wave == 0) {
+                double m;
+                const int c = plan_count<true, false>(sh, Dp, K, tstar, B, quota, sh.u.b.score, sh.u.b.node, m);
+                if (lane == 0) sh.cnt[0] = c;
+            }
+            __syncthreads();
         }
     } else if (mode == 2) {
-        const int c = sh.cnt[src];
-        const double* b = sh.u.buf + src * cap;
-        for (int i = tid; i < c; i += kPlanThreads) {
-            const double v = b[i];
-            int gt = 0, ge = 0;
-            for (int j = 0; j < c; ++j) {
-                const double w = b[j];
-                gt += w > v ? 1 : 0;
-                ge += w >= v ? 1 : 0;
+        // a listed node's places among the others, the comparisons split over
+        // the workgroup
+        src = __builtin_amdgcn_readfirstlane(src);
+        const int c = __builtin_amdgcn_readfirstlane(sh.cnt[src]);
+        const double* b = sh.u.b.score + src * cap;
+        const int cw = (c + kWave - 1) / kWave * kWave;
+        const int parts = max(1, kPlanThreads / cw);
+        const int len = (c + parts - 1) / parts;
+        for (int t = tid; t < cw * parts; t += kPlanThreads) {
+            const int part = t / cw, i = t - part * cw;
+            if (i < c) {
+                const double v = b[i];
+                const int j1 = min(c, (part + 1) * len);
+                int gt = 0, ge = 0;
+                for (int j = part * len; j < j1; ++j) {
+                    const double w = b[j];
+                    gt += w > v ? 1 : 0;
+                    ge += w >= v ? 1 : 0;
+                }
+                atomicAdd(&sh.map[i], gt << 16 | ge);
             }
+        }
+        __syncthreads();
+        for (int i = tid; i < c; i += kPlanThreads) {
+            const int gt = sh.map[i] >> 16, ge = sh.map[i] & 0xFFFF;
             if (gt <= B && ge >= B + 1) {  // every such thread holds the same value
-                sh.tstar = v;
+                sh.tstar = b[i];
                 sh.g = gt;
             }
         }
-    } else if (tid == 0) {
-        sh.tstar = -INFINITY;  // every node scores above it
-        sh.g = 0;
+        __syncthreads();
+        tstar = lane_f64(sh.tstar, 0);
+        quota = B - __builtin_amdgcn_readfirstlane(sh.g);
     }
-    __syncthreads();
-    if (wave != 0) return;
     if (stats && tid == 0) t_search = __builtin_amdgcn_s_memrealtime();
 
-    // ---- emission in BFS order (wave 0)
-    const double tstar = sh.tstar;
-    int quota = mode == 3 ? 0 : B - sh.g;  // nodes scoring exactly t* still admitted
-    bool tie_admitted = false;
+    // ---- emission: the list is in BFS order, so an admitted node's index is
+    // the number of admitted nodes before it (those scoring exactly t* are
+    // admitted in list order, up to the quota); one thread per listed node. By
+    // one wave, level by level and once more over the candidates, it took 7 us.
+    const int c = src >= 0 ? __builtin_amdgcn_readfirstlane(sh.cnt[src]) : 0;
+    const double* const ls = sh.u.b.score + max(src, 0) * cap;
+    const uint32_t* const ln = sh.u.b.node + max(src, 0) * cap;
+    constexpr int kChunks = (kPlanCapMax + kPlanThreads - 1) / kPlanThreads;
+    uint64_t bg[kChunks], be[kChunks];
     double minsc = INFINITY;
-    if (lane == 0) {
-        sh.u.t.score[0] = 0.0;
-        sh.u.t.par[0] = -1;
-        sh.u.t.rank[0] = -1;
-        sh.u.t.depth[0] = 0;
-    }
-    // lane l takes candidate l % K of parent l / K (as in plan_count); the
-    // admitted children of a parent are a prefix of its candidates
-    const int per = kWave / K;
-    const int pp = lane / K, pj = lane - pp * K;
-    int n = 1, plo = 0, phi = 1;
-    for (int k = 0; k < Dp && plo < phi; ++k) {
-        const int kk = sh.kfin[k];
-        const bool cand = pp < per && pj < kk;
-        const double lpj = cand ? (double)sh.lp[k * K + pj] : -INFINITY;
-        for (int base = plo; base < phi; base += per) {
-            const int i = base + pp;
-            const bool par_ok = pp < per && i < phi;
-            const bool valid = cand && i < phi;
-            const double s = par_ok ? sh.u.t.score[i] : 0.0;
-            const double cs = s + lpj;
-            const bool gt = valid && cs > tstar;
-            const bool eq = valid && cs == tstar;
-            // nodes scoring exactly t* are admitted in (depth, rank path) order,
-            // which is lane order here
-            const uint64_t beq = __ballot(eq);
-            const int etot = __popcll(beq);
-            const bool adm = gt || (eq && lanes_below(beq) < quota);
-            if (etot > 0 && quota > 0) tie_admitted = true;
-            quota -= min(etot, quota);
-            const uint64_t b = __ballot(adm);
-            if (adm) {
-                const int x = n + lanes_below(b);
-                if (x <= B) {  // always true: the admitted nodes number at most B
-                    sh.u.t.score[x] = cs;
-                    sh.u.t.par[x] = i;
-                    sh.u.t.rank[x] = pj;
-                    sh.u.t.depth[x] = k + 1;
-                    minsc = fmin(minsc, cs);
-                }
-            }
-            if (par_ok && pj == 0) {
-                const uint64_t seg = (K >= 64 ? ~0ull : ((1ull << K) - 1ull)) << (pp * K);
-                const int c = __popcll(b & seg);
-                sh.u.t.nch[i] = c;
-                sh.u.t.fc[i] = c ? n + __popcll(b & ((1ull << (pp * K)) - 1ull)) : -1;
-            }
-            n = min(n + __popcll(b), B + 1);
+#pragma unroll
+    for (int h = 0; h < kChunks; ++h) {
+        const int i = h * kPlanThreads + tid;
+        const double v = i < c ? ls[i] : -INFINITY;
+        bg[h] = __ballot(i < c && v > tstar);
+        be[h] = __ballot(i < c && v == tstar);
+        if (i < c && v > tstar) minsc = fmin(minsc, v);
+        const int sg = h * kPlanWaves + wave;
+        if (lane == 0 && sg < kPlanSegs) {
+            sh.seg_gt[sg] = __popcll(bg[h]);
+            sh.seg_eq[sg] = __popcll(be[h]);
         }
-        __threadfence_block();
-        plo = phi;
-        phi = n;
-    }
-    for (int i = plo + lane; i < phi; i += kWave) {  // the last level has no children
-        sh.u.t.nch[i] = 0;
-        sh.u.t.fc[i] = -1;
     }
     minsc = wave_min_f64(minsc);
-
+    if (lane == 0) sh.mins[wave] = minsc;
+    __syncthreads();
+    int gt_all = 0, eq_all = 0;
+    int gt_before[kChunks] = {}, eq_before[kChunks] = {};
+    for (int sg = 0; sg * kWave < c; ++sg) {
+        const int x = sh.seg_gt[sg], y = sh.seg_eq[sg];
+        gt_all += x;
+        eq_all += y;
+#pragma unroll
+        for (int h = 0; h < kChunks; ++h)
+            if (sg < h * kPlanWaves + wave) {
+                gt_before[h] += x;
+                eq_before[h] += y;
+            }
+    }
+    const bool tie_admitted = min(eq_all, quota) > 0;
+    const int n = 1 + gt_all + min(eq_all, quota);
+    int at[kChunks];  // the listed node's index in the tree (0: not admitted)
+#pragma unroll
+    for (int h = 0; h < kChunks; ++h) {
+        const int i = h * kPlanThreads + tid;
+        const int eb = eq_before[h] + lanes_below(be[h]);
+        const bool adm = ((bg[h] >> lane) & 1) || (((be[h] >> lane) & 1) && eb < quota);
+        at[h] = adm ? 1 + gt_before[h] + lanes_below(bg[h]) + min(eb, quota) : 0;
+        if (i < c) sh.map[i] = at[h];
+    }
+    __syncthreads();
     const size_t o = (size_t)r * (B + 1);
-    for (int i = lane; i < B + 1; i += kWave) {
-        if (i < n) {
-            tree.parent[o + i] = sh.u.t.par[i];
-            tree.depth[o + i] = sh.u.t.depth[i];
-            tree.rank[o + i] = sh.u.t.rank[i];
-            tree.score[o + i] = sh.u.t.score[i];
-            tree.n_children[o + i] = sh.u.t.nch[i];
-            tree.first_child[o + i] = sh.u.t.fc[i];
-        } else {
-            tree.parent[o + i] = -1;
-            tree.depth[o + i] = -1;
-            tree.rank[o + i] = -1;
-            tree.score[o + i] = 0.0;
-            tree.n_children[o + i] = 0;
-            tree.first_child[o + i] = -1;
+#pragma unroll
+    for (int h = 0; h < kChunks; ++h) {
+        const int i = h * kPlanThreads + tid;
+        const int x = at[h];
+        if (x > 0 && x <= B) {  // x <= B always: the admitted nodes number at most B
+            const uint32_t nd = ln[i];
+            const int p = (int)(nd >> 16);
+            const int par = p ? sh.map[p - 1] : 0;  // a parent is admitted before its children
+            tree.parent[o + x] = par;
+            tree.depth[o + x] = (int)(nd >> 8 & 0xFF);
+            tree.rank[o + x] = (int)(nd & 0xFF);
+            tree.score[o + x] = ls[i];
+            atomicAdd(&sh.nch[par], 1);
+            atomicMin(&sh.fc[par], x);
         }
     }
-    if (lane == 0) {
+    __syncthreads();
+    for (int i = tid; i < B + 1; i += kPlanThreads) {
+        const int m = i < n ? sh.nch[i] : 0;
+        tree.n_children[o + i] = m;
+        tree.first_child[o + i] = m ? sh.fc[i] : -1;
+        if (i == 0 || i >= n) {
+            tree.parent[o + i] = -1;
+            tree.depth[o + i] = i == 0 ? 0 : -1;
+            tree.rank[o + i] = -1;
+            tree.score[o + i] = 0.0;
+        }
+    }
+    if (tid == 0) {
         // margin: score of the B-th node in the order minus that of the (B+1)-th
+        for (int w = 1; w < kPlanWaves; ++w) minsc = fmin(minsc, sh.mins[w]);
         double margin = (double)INFINITY;
         if (mode != 3 && n > 1) margin = (tie_admitted ? tstar : minsc) - tstar;
         tree.n_nodes[r] = n;
