@@ -268,8 +268,8 @@ __device__ int pool_count(const PoolPlanShared& sh, const uint64_t* G, int P, in
             const bool ok = valid && cs >= tau;
             if (valid && !ok) m = fmax(m, cs);  // children below tau (the best of them counts)
             const uint64_t b = __ballot(ok);
-            const int cnt = __popcll(b);
-            if (total + cnt > cap) {
+            const int sum = __builtin_amdgcn_readfirstlane(total + __popcll(b));
+            if (sum > cap) {
                 m_out = -INFINITY;
                 return cap + 1;
             }
@@ -278,9 +278,9 @@ __device__ int pool_count(const PoolPlanShared& sh, const uint64_t* G, int P, in
                 bs[x] = cs;
                 bsl[x] = (uint8_t)list_slot(sh, G, K, li, pj);
             }
-            total += cnt;
+            total = sum;
         }
-        __threadfence_block();  // the next level reads these records from other lanes
+        wave_lds_fence();  // the next level reads these records from other lanes
         plo = nstart;
         phi = total;
         if (phi == plo) break;
@@ -298,10 +298,11 @@ __global__ __launch_bounds__(kPlanPoolThreads) void pool_plan(int D, int P, int 
     __shared__ PoolPlanShared sh;
     const int r = blockIdx.x;
     const int tid = threadIdx.x;
-    const int wave = tid / kWave, lane = tid % kWave;
+    // values alike in a wave's lanes are kept in scalar registers, as in plan_tree
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
     const int NL = 1 + (D - 1) * P;
     const uint64_t* G = lists + (size_t)r * NL * K;
-    const bool bad = (req_status[r] & TSB_REQ_NONFINITE) != 0;
+    const bool bad = (__builtin_amdgcn_readfirstlane(req_status[r]) & TSB_REQ_NONFINITE) != 0;
 
     // lists into LDS
     const int nent = min(NL * K, kPoolListLds);
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(kPlanPoolThreads) void pool_plan(int D, int P, int 
     // at the price of a round more now and then
     const int cap = (5 * (B + 1) + 3) / 4;
     const int ns = min(kPlanPoolWaves, kPoolPlanBuf / cap);
-    double hi_m = (Dp > 0 && sh.lnf[0] > 0) ? (double)sh.llp[0] : -INFINITY;  // the best node's score
+    double hi_m = lane_f64((Dp > 0 && sh.lnf[0] > 0) ? (double)sh.llp[0] : -INFINITY, 0);  // the best node's score
     int hi_cnt = 0;
     double lo = -INFINITY;
     int mode = 3;  // 1: t* = hi_m; 2: t* selected in a wave's buffer; 3: every node is chosen
@@ -334,8 +335,8 @@ __global__ __launch_bounds__(kPlanPoolThreads) void pool_plan(int D, int P, int 
         }
         if (wave < ns) {
             const double tau = wave == 0 ? hi_m
-                               : (lo > -INFINITY ? hi_m - (hi_m - lo) * ((double)wave / (double)ns)
-                                                 : hi_m - 0.25 * exp2(0.5 * (double)(wave - 1)));
+                               : (lo > -INFINITY ? hi_m - (hi_m - lo) * (double)((float)wave / (float)ns)
+                                                 : hi_m - ldexp((wave & 1) ? 0.25 : 0.25 * M_SQRT2, (wave - 1) >> 1));
             double m;
             const int c = pool_count(sh, G, P, Dp, K, tau, cap, sh.u.b.score + wave * cap, sh.u.b.slot + wave * cap, m);
             if (lane == 0) {
@@ -345,27 +346,29 @@ __global__ __launch_bounds__(kPlanPoolThreads) void pool_plan(int D, int P, int 
             }
         }
         __syncthreads();
-        if (sh.cnt[0] >= B + 1) {
+        // lane w holds wave w's count; thresholds fall from wave to wave, so the
+        // counts grow
+        const bool is_w = lane >= 1 && lane < ns;
+        const int cl = lane < ns ? sh.cnt[lane] : 0;
+        const double pl = lane < ns ? sh.piv[lane] : -INFINITY;
+        const double ml = lane < ns ? sh.mval[lane] : -INFINITY;
+        if (__builtin_amdgcn_readfirstlane(cl) >= B + 1) {
             mode = 1;
             break;
         }
-        int best = -1;
-        for (int w = 1; w < ns; ++w)
-            if (sh.cnt[w] >= B + 1 && sh.cnt[w] <= cap && (best < 0 || sh.piv[w] > sh.piv[best])) best = w;
-        if (best >= 0) {
+        const uint64_t hit = __ballot(is_w && cl >= B + 1 && cl <= cap);
+        if (hit) {
             mode = 2;
-            src = best;
+            src = __ffsll((unsigned long long)hit) - 1;
             break;
         }
-        int nh = 0;  // count(piv[0]) <= B here
-        double nlo = lo;
-        for (int w = 1; w < ns; ++w) {
-            if (sh.cnt[w] <= B && sh.piv[w] < sh.piv[nh]) nh = w;
-            if (sh.cnt[w] > cap && sh.piv[w] > nlo) nlo = sh.piv[w];
-        }
-        hi_cnt = sh.cnt[nh];
-        hi_m = sh.mval[nh];
-        lo = nlo;
+        // count(piv[0]) <= B here
+        const uint64_t low = __ballot(is_w && cl <= B && pl < lane_f64(pl, 0));
+        const uint64_t high = __ballot(is_w && cl > cap);
+        const int nh = low ? 63 - __clzll((long long)low) : 0;
+        hi_cnt = __builtin_amdgcn_readlane(cl, nh);
+        hi_m = lane_f64(ml, nh);
+        if (high) lo = fmax(lo, lane_f64(pl, __ffsll((unsigned long long)high) - 1));
         __syncthreads();
     }
     if (mode == 1) {
@@ -374,7 +377,7 @@ __global__ __launch_bounds__(kPlanPoolThreads) void pool_plan(int D, int P, int 
             sh.g = hi_cnt;
         }
     } else if (mode == 2) {
-        const int c = sh.cnt[src];
+        const int c = __builtin_amdgcn_readfirstlane(sh.cnt[src]);
         const double* b = sh.u.b.score + src * cap;
         for (int i = tid; i < c; i += kPlanPoolThreads) {
             const double v = b[i];
@@ -398,8 +401,8 @@ __global__ __launch_bounds__(kPlanPoolThreads) void pool_plan(int D, int P, int 
 
     // ---- emission in BFS order (wave 0): lane l takes candidate l % K of
     // parent l / K; the admitted children of a parent are a prefix of its list
-    const double tstar = sh.tstar;
-    int quota = mode == 3 ? 0 : B - sh.g;  // nodes scoring exactly t* still admitted
+    const double tstar = lane_f64(sh.tstar, 0);
+    int quota = mode == 3 ? 0 : B - __builtin_amdgcn_readfirstlane(sh.g);  // nodes scoring exactly t* still admitted
     bool tie_admitted = false;
     double minsc = INFINITY;
     if (lane == 0) {
@@ -429,7 +432,7 @@ __global__ __launch_bounds__(kPlanPoolThreads) void pool_plan(int D, int P, int 
             const int etot = __popcll(beq);
             const bool adm = gt || (eq && lanes_below(beq) < quota);
             if (etot > 0 && quota > 0) tie_admitted = true;
-            quota -= min(etot, quota);
+            quota = __builtin_amdgcn_readfirstlane(quota - min(etot, quota));
             const uint64_t b = __ballot(adm);
             if (adm) {
                 const int x = n + lanes_below(b);
@@ -448,7 +451,7 @@ __global__ __launch_bounds__(kPlanPoolThreads) void pool_plan(int D, int P, int 
                 sh.u.t.nch[i] = c;
                 sh.u.t.fc[i] = c ? n + __popcll(b & ((1ull << (pp * K)) - 1ull)) : -1;
             }
-            n = min(n + __popcll(b), B + 1);
+            n = __builtin_amdgcn_readfirstlane(min(n + __popcll(b), B + 1));
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         plo = phi;
