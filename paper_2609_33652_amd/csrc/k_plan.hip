@@ -1356,7 +1356,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_tree(int D, int S, int K, i
 // sits at f * K_d + j), so the storage order is the order of (depth, path):
 // ties on score are resolved by storage index, and the chosen nodes in
 // storage order are the BFS order of the tree.
-constexpr int kEpMax = 6144;  // generated nodes held in LDS
+constexpr int kEpMax = 6144;   // generated nodes held in LDS
+constexpr int kEpPlaces = 256;  // largest layer whose places are counted by the workgroup
 
 struct EpShared {
     float lp[TSB_MAX_D * TSB_MAX_K];
@@ -1371,8 +1372,7 @@ struct EpShared {
     uint8_t depth[kEpMax];
     uint8_t flag[kEpMax];
     int16_t front[kEpFrontierLimit];
-    int lstart[TSB_MAX_D + 1];
-    uint64_t lists[kPlanWaves][kWave];
+    int place[kEpPlaces];  // a layer's places by (score desc, path); 0 between layers
     uint32_t hist[256];
     int wsum[kPlanWaves];
     double wmax[kPlanWaves];
@@ -1434,18 +1434,20 @@ __global__ __launch_bounds__(kPlanThreads) void plan_ep(int D, int S, int K, int
     __shared__ EpShared sh;
     const int r = blockIdx.x;
     const int tid = threadIdx.x;
-    const int wave = tid / kWave, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
 
     if (tid == 0) sh.bad = 0;
+    if (tid < kEpPlaces) sh.place[tid] = 0;
     __syncthreads();
     for (int d = wave; d < D; d += kPlanWaves)
         merge_row(sh, r * D + d, d, S, K, invT, pm, ps, pk, pf, draft_lse, topk_tok, topk_lp);
     __syncthreads();
-    const bool nonfinite = sh.bad != 0;
+    const bool nonfinite = __builtin_amdgcn_readfirstlane(sh.bad) != 0;
     const int Dp = nonfinite ? 0 : D;
+    const int kfin = lane < D ? sh.kfin[lane] : 0;
 
     // layer of depth 1: the root's candidates
-    const int k0 = Dp > 0 ? sh.kfin[0] : 0;
+    const int k0 = Dp > 0 ? __builtin_amdgcn_readfirstlane(kfin) : 0;
     for (int i = tid; i < k0; i += kPlanThreads) {
         sh.score[i] = (double)sh.lp[i];
         sh.par[i] = -1;
@@ -1453,71 +1455,79 @@ __global__ __launch_bounds__(kPlanThreads) void plan_ep(int D, int S, int K, int
         sh.depth[i] = 1;
         sh.flag[i] = 0;
     }
-    if (tid == 0) {
-        sh.lstart[0] = 0;
-        sh.lstart[1] = k0;
-    }
-    int ntot = k0, layers = k0 > 0 ? 1 : 0;
+    int ntot = k0;
     __syncthreads();
 
-    // expansion (wave 0 alone: a layer holds at most frontier * K nodes):
-    // frontier of each layer, then its children
-    if (wave == 0) {
-        for (int d = 1; d < Dp; ++d) {
-            const int lb = sh.lstart[d - 1], le = sh.lstart[d], nl = le - lb, kd = sh.kfin[d];
-            if (nl == 0 || kd == 0) break;
-            int f = 0;  // frontier nodes, listed in lexicographic (storage) order
+    // expansion: frontier of each layer, then its children. The workgroup
+    // counts every node's place in its layer (comparisons split over the
+    // threads), wave 0 lists the frontier and writes the children: the layers
+    // follow one another, and a 128-key sort by one wave was most of a layer's
+    // time (16 x 129 nodes, 15 layers of 100: launch 62.6 us with it, 52.5 so).
+    for (int d = 1, lb = 0, le = k0; d < Dp; ++d) {
+        const int nl = le - lb, kd = __builtin_amdgcn_readlane(kfin, d);
+        if (nl == 0 || kd == 0) break;
+        const int f = min(nl, W);  // frontier nodes
+        if (le + f * kd > kEpMax) break;  // the host bounds the generated nodes; never taken
+        const bool counted = nl > W && nl <= kEpPlaces;
+        if (counted) {
+            const int cw = (nl + kWave - 1) / kWave * kWave;
+            const int parts = kPlanThreads / cw, len = (nl + parts - 1) / parts;
+            const int part = tid / cw, i = tid - part * cw;
+            if (part < parts && i < nl) {
+                const double v = sh.score[lb + i];
+                const int j1 = min(nl, (part + 1) * len);
+                int before = 0;
+                for (int j = part * len; j < j1; ++j) {
+                    const double w = sh.score[lb + j];
+                    before += w > v || (w == v && j < i) ? 1 : 0;
+                }
+                atomicAdd(&sh.place[i], before);
+            }
+            __syncthreads();
+        }
+        if (wave == 0) {
+            // frontier nodes, listed in lexicographic (storage) order
             if (nl <= W) {
+                for (int i = lane; i < nl; i += kWave) sh.front[i] = (int16_t)(lb + i);
+            } else if (counted) {
+                int o = 0;
+                for (int base = 0; base < nl; base += kWave) {
+                    const int i = base + lane;
+                    const bool in = i < nl && sh.place[i] < W;
+                    if (i < nl) sh.place[i] = 0;
+                    const uint64_t ib = __ballot(in);
+                    if (in) sh.front[o + lanes_below(ib)] = (int16_t)(lb + i);
+                    o += __popcll(ib);
+                }
+            } else {
+                // the W-th largest score of the layer (with multiplicity)
+                WaveTopList tl;
+                tl.init(W);
                 for (int base = lb; base < le; base += kWave) {
                     const int i = base + lane;
-                    if (i < le) sh.front[i - lb] = (int16_t)i;
+                    tl.offer(i < le ? ordered_bits64(sh.score[i]) : 0ull, i < le);
                 }
-                f = nl;
-            } else {
-                // the W-th largest score of the layer (with multiplicity): a
-                // sort of the layer's keys when it holds at most 128 nodes
-                uint64_t tk;
-                if (nl <= 2 * kWave && W <= kWave) {
-                    uint64_t v[2];
-#pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        const int i = lb + q * kWave + lane;
-                        v[q] = i < le ? ordered_bits64(sh.score[i]) : 0ull;
-                    }
-                    wave_sort_desc<2>(v);
-                    tk = lane_u64(v[0], W - 1);
-                } else {  // inserts (measured no slower than a 256-key sort)
-                    WaveTopList tl;
-                    tl.init(W);
-                    for (int base = lb; base < le; base += kWave) {
-                        const int i = base + lane;
-                        tl.offer(i < le ? ordered_bits64(sh.score[i]) : 0ull, i < le);
-                    }
-                    tk = lane_u64(tl.v, W - 1);
-                }
+                const uint64_t tk = lane_u64(tl.v, W - 1);
                 int above = 0;
                 for (int base = lb; base < le; base += kWave) {
                     const int i = base + lane;
                     above += __popcll(__ballot(i < le && ordered_bits64(sh.score[i]) > tk));
                 }
                 // nodes above the W-th score, then ties in lexicographic order
-                int ties = 0;
+                int o = 0, ties = 0;
                 for (int base = lb; base < le; base += kWave) {
                     const int i = base + lane;
                     const uint64_t k = i < le ? ordered_bits64(sh.score[i]) : 0ull;
                     const bool tie = i < le && k == tk;
                     const uint64_t tb = __ballot(tie);
-                    const int trank = ties + __popcll(tb & ((1ull << lane) - 1ull));
-                    const bool in = (i < le && k > tk) || (tie && trank < W - above);
+                    const bool in = (i < le && k > tk) || (tie && ties + lanes_below(tb) < W - above);
                     const uint64_t ib = __ballot(in);
-                    if (in) sh.front[f + __popcll(ib & ((1ull << lane) - 1ull))] = (int16_t)i;
-                    f += __popcll(ib);
+                    if (in) sh.front[o + lanes_below(ib)] = (int16_t)i;
+                    o += __popcll(ib);
                     ties += __popcll(tb);
                 }
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (le + f * kd > kEpMax) break;  // the host bounds the generated nodes; never taken
+            wave_lds_fence();
             for (int t = lane; t < f * kd; t += kWave) {
                 const int p = sh.front[t / kd], j = t % kd;
                 const int c = le + t;
@@ -1527,17 +1537,12 @@ __global__ __launch_bounds__(kPlanThreads) void plan_ep(int D, int S, int K, int
                 sh.depth[c] = (uint8_t)(d + 1);
                 sh.flag[c] = 0;
             }
-            if (lane == 0) sh.lstart[d + 1] = le + f * kd;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            ntot = le + f * kd;
-            layers = d + 1;
         }
-        if (lane == 0) sh.cnt = ntot;
+        __syncthreads();
+        lb = le;
+        le += f * kd;
+        ntot = le;
     }
-    __syncthreads();
-    ntot = sh.cnt;
-    __syncthreads();
     for (int i = tid; i < ntot; i += kPlanThreads) sh.flag[i] &= (uint8_t)~(kEpFront | kEpTie);
     __syncthreads();
 
@@ -1676,7 +1681,6 @@ __global__ __launch_bounds__(kPlanThreads) void plan_ep(int D, int S, int K, int
         else if (n < B + 1) st |= TSB_REQ_BUDGET_SHORT;
         req_status[r] = st;
     }
-    (void)layers;
 }
 
 // ------------------------------------------------------------------ launch

@@ -3,7 +3,9 @@ parent list can go wrong: budgets around a wave's and the workgroup's width and
 the largest one, rows whose candidates need one, two and more registers to
 merge, scores past the widest histogram (no first guess), more tied nodes than
 a counting buffer holds, trees short of their budget, and batches whose nodes
-take one and several workgroups of the parent list.
+take one and several workgroups of the parent list. For expand-then-prune:
+layers narrower than the frontier, of the largest size whose places the whole
+workgroup counts, and past it, with and without ties.
 
 Topology, scores and margin must equal the oracle's planner on the same
 log-probabilities, bit for bit; the replay must give every listed parent's
@@ -15,6 +17,7 @@ import torch
 
 import paper_2609_33652_amd as tsb
 from oracle import planner as oplan
+from oracle import planner_ep as oplan_ep
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +81,30 @@ def test_plan_and_parent_list(V, R, D, B, K, kind, dtype):
                 m, f = int(h["n_children"][r, u]), int(h["first_child"][r, u])
                 if m:
                     assert len(set(h["node_tok"][r, f:f + m].tolist())) == m
+
+
+@pytest.mark.parametrize("D,B,K,W,kind", [
+    (6, 40, 4, 4, "mixed"),
+    (5, 100, 8, 8, "steps"),
+    (6, 300, 16, 16, "mixed"),
+    (6, 300, 16, 16, "flat"),
+    (5, 300, 20, 13, "mixed"),
+    (5, 300, 20, 13, "steps"),
+    (9, 100, 6, 10, "short"),
+])
+def test_expand_prune_layers(D, B, K, W, kind):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    R, V = 2, 600
+    g = torch.Generator().manual_seed(B + K)
+    draft = _draft(kind, R, D, V, g).cuda()
+    rnd = tsb.Round(tsb.make_config(R, D, V, B, K, 1.0, "f32", 3), "cuda")
+    rnd.plan_ep(draft, W)
+    h = rnd.host()
+    for r in range(R):
+        ref = oplan_ep.plan_expand_prune(h["topk_lp"][r].numpy(), B, W)
+        n = ref["n_nodes"]
+        assert int(h["n_nodes"][r]) == n
+        for k in ("parent", "depth", "rank", "n_children", "first_child", "score"):
+            assert np.array_equal(h[k][r, :n].numpy(), ref[k]), (r, k)
+        assert float(h["plan_margin"][r]) == ref["plan_margin"]
