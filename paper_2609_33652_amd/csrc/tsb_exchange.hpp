@@ -3,8 +3,8 @@
 //
 // Layout (a workspace region): slots [R][2][kWalkGroupsMax][kSlotWords]
 // 64-bit words; round e of request r uses the slot pair of parity e & 1. A
-// publisher (thread 0 of a workgroup) writes each word with one relaxed
-// agent-scope store; every word carries the round's 8-bit tag in its low
+// publisher (thread 0 of a workgroup, or a lane of its wave 0 per word) writes
+// each word with one relaxed agent-scope store; every word carries the round's 8-bit tag in its low
 // bits, so a reader knows it holds all words of the current round without
 // any ordering between the stores:
 //   tag(e) = (e & 1) << 7 | ((e >> 1) % 127 + 1)
