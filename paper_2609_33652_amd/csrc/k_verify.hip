@@ -22,6 +22,7 @@
 // at an accepted leaf).
 #include <math.h>
 
+#include <algorithm>
 #include <atomic>
 
 #include "tsb_device.hpp"
@@ -1704,12 +1705,22 @@ static hipError_t launch_chain_rows(const tsb_config& c, float invT, const void*
     return hipGetLastError();
 }
 
-// LDS of a walk workgroup's slice (one recomputed in every pass needs none),
-// and what capacity is asked with: the largest a launch may need.
-static size_t walk_lds(const tsb_config& c, int G) {
-    const int span = walk_span(c.V, G);
-    return span <= kWalkHeldTokens ? (size_t)span * 2 * sizeof(double) : 0;
+// Workgroups per request of a walk, at most the resident ones of its kernel
+// (the tickets need those of one request to fit on the device at once), and
+// the LDS of the slices that this many leave: the kernel works its slice out
+// from the same G (a slice recomputed in every pass needs no LDS).
+struct WalkShape {
+    int G;
+    size_t lds;
+};
+static WalkShape walk_shape(const tsb_config& c, int resident) {
+    WalkShape w;
+    w.G = std::min(geometry(c).G, resident);
+    const int span = walk_span(c.V, w.G);
+    w.lds = span <= kWalkHeldTokens ? (size_t)span * 2 * sizeof(double) : 0;
+    return w;
 }
+// What residency is asked with: the largest LDS a launch may need.
 constexpr size_t kWalkLdsMax = (size_t)kWalkHeldTokens * 2 * sizeof(double);
 constexpr size_t trav_stack_bytes(int D) { return (size_t)(D + 1) * sizeof(TravState); }
 
@@ -1754,10 +1765,10 @@ static WalkArgs walk_args(const tsb_config& c, float invT, const void* draft, co
 
 // One launch of a walk grid: G workgroups per request, each taking its
 // (request, slice) from a ticket (xticket), so only G workgroups need to fit
-// on the device at once (cap: resident workgroups of this kernel).
-static hipError_t launch_walk_grid(const void* fn, WalkArgs& A, int R, int G0, int cap, size_t lds, hipStream_t st) {
+// on the device at once.
+static hipError_t launch_walk_grid(const void* fn, WalkArgs& A, int R, int G, size_t lds, hipStream_t st) {
     A.R = R;
-    A.G = G0 < cap ? G0 : cap;
+    A.G = G;
     void* args[] = {&A};
     return hipLaunchKernel(fn, dim3((unsigned)(A.G * R)), dim3(kWalkThreads), args, lds, st);
 }
@@ -1785,13 +1796,12 @@ hipError_t launch_verify(const tsb_config& c, float invT, const void* draft, con
     const bool bf16 = c.dtype == TSB_BF16;
     const void* fn = bf16 ? (vec4 ? (const void*)verify_walk<TSB_BF16, true> : (const void*)verify_walk<TSB_BF16, false>)
                           : (vec4 ? (const void*)verify_walk<TSB_F32, true> : (const void*)verify_walk<TSB_F32, false>);
-    const int G = geometry(c).G;
-    const size_t lds = walk_lds(c, G);
     int cap = 0;
     if ((e = walk_capacity(fn, 0, bf16 ? 1 : 0, vec4 ? 1 : 0, kWalkLdsMax, &cap)) != hipSuccess) return e;
     if (cap < 1) return hipErrorLaunchOutOfResources;
+    const WalkShape shape = walk_shape(c, cap);
     if ((e = hook_before(TSB_KERNEL_VERIFY_WALK, st)) != hipSuccess) return e;
-    if ((e = launch_walk_grid(fn, A, c.R, G, cap, lds, st)) != hipSuccess) return e;
+    if ((e = launch_walk_grid(fn, A, c.R, shape.G, shape.lds, st)) != hipSuccess) return e;
     return hook_after(TSB_KERNEL_VERIFY_WALK, st);
 }
 
@@ -1809,13 +1819,12 @@ hipError_t launch_verify_traversal(const tsb_config& c, float invT, const void* 
     const bool bf16 = c.dtype == TSB_BF16;
     const void* fn = bf16 ? (vec4 ? (const void*)verify_traversal<TSB_BF16, true> : (const void*)verify_traversal<TSB_BF16, false>)
                           : (vec4 ? (const void*)verify_traversal<TSB_F32, true> : (const void*)verify_traversal<TSB_F32, false>);
-    const int G = geometry(c).G;
-    const size_t lds = walk_lds(c, G) + trav_stack_bytes(c.D);
     int cap = 0;
     if ((e = walk_capacity(fn, 2, bf16 ? 1 : 0, vec4 ? 1 : 0, kWalkLdsMax + trav_stack_bytes(TSB_MAX_D), &cap)) != hipSuccess) return e;
     if (cap < 1) return hipErrorLaunchOutOfResources;
+    const WalkShape shape = walk_shape(c, cap);
     if ((e = hook_before(TSB_KERNEL_TRAVERSAL_WALK, st)) != hipSuccess) return e;
-    if ((e = launch_walk_grid(fn, A, c.R, G, cap, lds, st)) != hipSuccess) return e;
+    if ((e = launch_walk_grid(fn, A, c.R, shape.G, shape.lds + trav_stack_bytes(c.D), st)) != hipSuccess) return e;
     return hook_after(TSB_KERNEL_TRAVERSAL_WALK, st);
 }
 
@@ -1851,7 +1860,7 @@ hipError_t launch_pool_verify(const tsb_config& c, int P, float invT, const void
     const size_t lds = (size_t)((span + 31) / 32) * sizeof(uint32_t);
     if (lds > lds_max) return hipErrorInvalidConfiguration;  // vocabulary too wide for the slice bitmap
     if ((e = hook_before(TSB_KERNEL_POOL_WALK, st)) != hipSuccess) return e;
-    if ((e = launch_walk_grid(fn, A, c.R, G, cap, lds, st)) != hipSuccess) return e;
+    if ((e = launch_walk_grid(fn, A, c.R, G, lds, st)) != hipSuccess) return e;
     return hook_after(TSB_KERNEL_POOL_WALK, st);
 }
 
