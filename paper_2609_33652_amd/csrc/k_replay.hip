@@ -633,8 +633,9 @@ __device__ __forceinline__ void scan_item(const ScanArgs& A, long long it, int l
                 listed = true;
                 hn = 0;
                 // with m keys kept, the tile's m-th best is a bound too: fewer
-                // of the groups after these pass
-                if (top.thr != 0ull && cand_value(top.thr) > I.thr) {
+                // of the groups after these pass (a parent that is not pruned
+                // keeps its -inf: every token of its row is scored)
+                if (I.thr > -INFINITY && top.thr != 0ull && cand_value(top.thr) > I.thr) {
                     I.thr = cand_value(top.thr);
                     I.bound = I.thr - kGumbelMaxBound;
                     wt.init(I.thr, I.cd, invT);

@@ -78,3 +78,27 @@ def test_scan_edges(V, R, B, K, kind, dtype, T):
             assert np.array_equal(h["node_tok"][r, fc:fc + m].numpy(), toks), (r, u, m)
             checked += 1
     assert checked > 0
+
+
+@pytest.mark.parametrize("K,bad", [(32, False), (6, False), (6, True)])
+def test_unpruned_rows_are_scored_whole(K, bad):
+    """Without pruning (by the flag, or for a parent whose candidates repeat) every group of four tokens of the
+    scanned rows draws its words and has its keys evaluated, whatever was kept before it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    R, D, V, B = 2, 3, 20000, 40
+    dev = _rows("flat", R, D, V, torch.Generator().manual_seed(K)).to(torch.bfloat16).cuda()
+    rnd = tsb.Round(tsb.make_config(R, D, V, B, K, 1.0, "bf16", 5, 0 if bad else tsb.FLAG_NO_PRUNE), "cuda")
+    rnd.plan(dev)
+    if bad:
+        rnd.topk_tok[:, :, 1] = rnd.topk_tok[:, :, 0]
+    tsb.stats_enable(True)
+    try:
+        tsb.stats_read()
+        rnd.replay(dev, 3)
+        s = tsb.stats_read()
+    finally:
+        tsb.stats_enable(False)
+    parents = int((rnd.host()["n_children"] > 0).sum())
+    assert s["replay_tokens"] == parents * V
+    assert s["replay_groups_live"] == s["replay_groups_keyed"] == parents * V // 4
