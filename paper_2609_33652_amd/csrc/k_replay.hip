@@ -781,18 +781,16 @@ __global__ __launch_bounds__(kWave) void replay_merge(int B, int D, int K, int T
         if (job.nrec) write_record<DT>(job.nrec, head, draft, job.target, V, D, invT, r, tb + u, tok, lane);
     };
     const size_t o = (tb + u) * (size_t)T;
-    if (T <= kWave) {
-        // lane t holds tile t's count; the keys of all slots (in no order) are
-        // gathered contiguously, their indices placed through LDS, and loaded
-        // together, up to kMergeKeys a lane. The m-th largest of the lane
-        // maxima is a lower bound of the m-th key (lanes hold distinct keys):
-        // the few keys that reach it are compacted, one per lane, and a key's
-        // rank is the number of larger ones. (A sort of 64 keys takes about
-        // 1.3 us here, an insert 0.15 us.)
-        constexpr int kMergeKeys = 12;
-        __shared__ uint16_t s_idx[kWave * TSB_MAX_K];
-        __shared__ uint64_t s_key[kWave];
-        const int ct = lane < T ? cc[o + lane] : 0;
+    // 64 tiles at a time, lane t holds tile t's count; the keys of their slots
+    // (in no order) are gathered contiguously, their indices placed through LDS
+    // (reading every slot of 65 tiles took 21.5 us for one request of 65 nodes
+    // and 29.3 for 16 of 129, gathering them 12.0 and 18.6)
+    __shared__ uint16_t s_idx[kWave * TSB_MAX_K];
+    __shared__ uint64_t s_key[kWave];
+    WaveTopList top;
+    top.init(m);
+    for (int t0 = 0; t0 < T; t0 += kWave) {
+        const int ct = t0 + lane < T ? cc[o + t0 + lane] : 0;
         int nv = 0;
         for (int j = 0;; ++j) {
             const uint64_t bj = __ballot(j < ct);
@@ -801,8 +799,14 @@ __global__ __launch_bounds__(kWave) void replay_merge(int B, int D, int K, int T
             nv += __popcll(bj);
         }
         wave_lds_fence();
-        const uint64_t* cb = cand + o * TSB_MAX_K;
-        if (nv <= kMergeKeys * kWave) {
+        const uint64_t* cb = cand + (o + t0) * TSB_MAX_K;
+        // the keys are loaded together, up to kMergeKeys a lane. The m-th
+        // largest of the lane maxima is a lower bound of the m-th key (lanes hold
+        // distinct keys): the few keys that reach it are compacted, one per lane,
+        // and a key's rank is the number of larger ones. (A sort of 64 keys takes
+        // about 1.3 us here, an insert 0.15 us.)
+        constexpr int kMergeKeys = 12;
+        if (T <= kWave && nv <= kMergeKeys * kWave) {
             uint64_t kb[kMergeKeys], mx = 0ull;
 #pragma unroll
             for (int q = 0; q < kMergeKeys; ++q) {
@@ -843,10 +847,8 @@ __global__ __launch_bounds__(kWave) void replay_merge(int B, int D, int K, int T
                 return;
             }
         }
-        // more keys than that (or ties of their upper halves): inserted in
-        // batches of 64, the loads of several in flight together
-        WaveTopList top;
-        top.init(m);
+        // more keys than that, ties of their upper halves, or more tiles:
+        // inserted in batches of 64, the loads of several in flight together
         constexpr int kMergeBatches = 8;
         for (int b0 = 0; b0 < nv; b0 += kMergeBatches * kWave) {
             uint64_t kb[kMergeBatches];
@@ -858,19 +860,7 @@ __global__ __launch_bounds__(kWave) void replay_merge(int B, int D, int K, int T
 #pragma unroll
             for (int q = 0; q < kMergeBatches; ++q) top.offer(kb[q], kb[q] != 0);
         }
-        finish((int32_t)cand_id(top.v));
-        return;
-    }
-    WaveTopList top;
-    top.init(m);
-    // the tiles' slots, two tiles a batch
-    const int ne = T * TSB_MAX_K;
-    for (int base = 0; base < ne; base += kWave) {
-        const int i = base + lane;
-        const int tt = i / TSB_MAX_K, j = i % TSB_MAX_K;
-        uint64_t k = 0;
-        if (i < ne && j < cc[o + tt]) k = cand[(o + tt) * TSB_MAX_K + j];
-        top.offer(k, k != 0);
+        wave_lds_fence();  // the next tiles' indices take their place
     }
     finish((int32_t)cand_id(top.v));
 }

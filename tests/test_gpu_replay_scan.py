@@ -1,7 +1,9 @@
 """The replay scan where its branches can go wrong: rows around one tile and
 around the shortest sampled row, with and without vector loads; flat rows
 (whose hits overflow the list of hits, and whose keys exceed a tile's slots),
-peaked and masked ones; calls with and without the sampled threshold.
+peaked and masked ones; calls with and without the sampled threshold. Rows of
+more keys than the merge ranks at once, and of 64 tiles (a lane each), 65 and
+two times 64 and a part.
 
 Every parent's children are compared with the binary64 oracle (a decision
 whose margin is below 1e-5, the binary32 key's resolution, is left out, as in
@@ -46,7 +48,11 @@ def _rows(kind, R, D, V, g):
     (40008, 4, 64, 12, "peaked", "bf16", 0.8),
     (40008, 4, 64, 12, "masked", "bf16", 1.0),
     (40008, 1, 64, 12, "flat", "bf16", 1.0),
+    (131072, 1, 64, 32, "flat", "bf16", 1.0),
+    (262144, 1, 255, 24, "flat", "bf16", 1.0),
+    (262208, 1, 64, 8, "mixed", "bf16", 1.0),
     (270336, 1, 255, 16, "flat", "bf16", 1.0),
+    (528388, 1, 64, 8, "flat", "bf16", 1.0),
 ])
 def test_scan_edges(V, R, B, K, kind, dtype, T):
     if not torch.cuda.is_available():
@@ -64,6 +70,10 @@ def test_scan_edges(V, R, B, K, kind, dtype, T):
         got.append(rnd.host())
     h = got[0]
     assert torch.equal(h["node_tok"], got[1]["node_tok"])
+    tiles = -(-V // 4096)
+    if 25 <= tiles <= 64:
+        # unpruned, a tile of a flat row fills its parent's slots: more keys than the merge ranks at once (768)
+        assert int(h["n_children"].max()) * tiles > 768
     a = (draft.float() * (torch.tensor(1.0) / torch.tensor(T))).double().numpy()
     checked = 0
     for r in range(R):
