@@ -4,10 +4,10 @@
 // (Gumbel-top-k = ordered sampling without replacement).
 //
 //   replay_threshold  one wave per parent: a lower bound of its m-th key
-//                 from its planning candidates and a sample of the row; a
-//                 workgroup per 2048 nodes writes
-//                 the flat list of the parents of the batch (request-major,
-//                 BFS order, so a depth's parents are contiguous).
+//                 from its planning candidates and a sample of the row; the
+//                 first workgroups write the flat list of the parents of the
+//                 batch (request-major, BFS order, so a depth's parents are
+//                 contiguous).
 //   replay_scan   one wave per (parent, vocabulary tile) item, dealt
 //                 grid-stride over a persistent grid (parents of one (request,
 //                 depth) are adjacent, so their tiles of draft row d meet in
@@ -63,14 +63,29 @@ __device__ __forceinline__ bool replay_parent(const tsb_tree& tree, int r, int u
     return nd->ok && nd->m > 0 && nd->m <= K;
 }
 
-// Nodes of the parent list that one workgroup writes. A workgroup counts the
-// parents before its own nodes itself instead of waiting for the others: a
-// chunk counted is a chunk of loads (all in flight together), a chunk written
-// by the same workgroup before was a serial step of 4 us (16448 nodes: the
-// launch 39.1 us with one workgroup, 20.4 with nine; 2064 nodes: 10.3 either
-// way, the thresholds' own time).
+// The parent list is written in chunks of kListNodes nodes, one to a workgroup
+// for up to kListGroups chunks (65536 nodes), equal runs of chunks beyond. A
+// workgroup counts the parents before its own chunks itself instead of waiting
+// for the others: a chunk counted is a chunk of loads (all in flight together),
+// a chunk written by the same workgroup before was a serial step of 4 us (16448
+// nodes: the launch 39.1 us with one workgroup, 20.4 with nine; 2064 nodes:
+// 10.3 either way, the thresholds' own time). With a workgroup for every chunk
+// the counting grows with the square of the nodes: a replay of 4.2 M nodes took
+// 9.5 ms, 8.4 M 32.3 (with runs of chunks 5.4 and 11.0, whether in 32, 64 or 128
+// workgroups).
 constexpr int kListPer = 8;
 constexpr int kListNodes = kBlock * kListPer;
+constexpr int kListGroups = 32;
+struct ListSplit {
+    int chunks, per, groups;  // chunks in all, of a workgroup, and workgroups
+};
+static ListSplit list_split(int nodes) {
+    ListSplit l;
+    l.chunks = (nodes + kListNodes - 1) / kListNodes;
+    l.per = (l.chunks + kListGroups - 1) / kListGroups;
+    l.groups = (l.chunks + l.per - 1) / l.per;
+    return l;
+}
 
 // Which of nodes i0 + k * 64 + lane (k < kListPer) are parents: bit `lane` of
 // par[k]. Every entry is loaded before any is tested (replay_parent's
@@ -101,44 +116,48 @@ __device__ __forceinline__ void list_parents(int i0, int total_nodes, int B, int
 
 // Flat list of every parent, request-major, BFS order within a request (so
 // parents of one (request, depth) are contiguous): plist[i] =
-// r * (B + 1) + u; ptotal[0] = list length. Workgroup `chunk` of `chunks`
-// writes the parents of its kListNodes nodes (a wave kListPer * 64 of them).
-__device__ void prep_list(int chunk, int chunks, int R, int B, int D, int K, const tsb_tree& tree,
+// r * (B + 1) + u; ptotal[0] = list length. Workgroup `group` writes the
+// parents of its chunks (a wave kListPer * 64 nodes of each).
+__device__ void prep_list(int group, const ListSplit& L, int R, int B, int D, int K, const tsb_tree& tree,
                           int* __restrict__ plist, int* __restrict__ ptotal) {
-    __shared__ int s_before[kBlock / kWave], s_own[kBlock / kWave];
+    __shared__ int s_before[kBlock / kWave], s_own[2][kBlock / kWave];
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const int total_nodes = R * (B + 1);
+    const int c0 = group * L.per, c1 = min(L.chunks, c0 + L.per);
     uint64_t par[kListPer];
     int before = 0;
-    for (int c = 0; c < chunk; ++c) {
+    for (int c = 0; c < c0; ++c) {
         list_parents(c * kListNodes + wave * kListPer * kWave, total_nodes, B, D, K, tree, par);
 #pragma unroll
         for (int k = 0; k < kListPer; ++k) before += __popcll(par[k]);
     }
-    const int i0 = chunk * kListNodes + wave * kListPer * kWave;
-    list_parents(i0, total_nodes, B, D, K, tree, par);
-    int own = 0;
+    int base = 0;
+    for (int c = c0; c < c1; ++c) {
+        const int i0 = c * kListNodes + wave * kListPer * kWave;
+        list_parents(i0, total_nodes, B, D, K, tree, par);
+        int own = 0;
 #pragma unroll
-    for (int k = 0; k < kListPer; ++k) own += __popcll(par[k]);
-    if (lane == 0) {
-        s_before[wave] = before;
-        s_own[wave] = own;
-    }
-    __syncthreads();
-    int o = 0, end = 0;
-    for (int w = 0; w < kBlock / kWave; ++w) {
-        o += s_before[w] + (w < wave ? s_own[w] : 0);
-        end += s_before[w] + s_own[w];
-    }
+        for (int k = 0; k < kListPer; ++k) own += __popcll(par[k]);
+        int* const s = s_own[(c - c0) & 1];  // one barrier a chunk: the next one writes the other
+        if (lane == 0) {
+            s[wave] = own;
+            s_before[wave] = before;
+        }
+        __syncthreads();
+        if (c == c0)
+            for (int w = 0; w < kBlock / kWave; ++w) base += s_before[w];
+        int o = base;
+        for (int w = 0; w < kBlock / kWave; ++w) {
+            o += w < wave ? s[w] : 0;
+            base += s[w];
+        }
 #pragma unroll
-    for (int k = 0; k < kListPer; ++k) {
-        if ((par[k] >> lane) & 1)
-            plist[o + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(par[k] >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)par[k], 0u))] =
-                i0 + k * kWave + lane;
-        o += __popcll(par[k]);
+        for (int k = 0; k < kListPer; ++k) {
+            if ((par[k] >> lane) & 1) plist[o + lanes_below_u64(par[k])] = i0 + k * kWave + lane;
+            o += __popcll(par[k]);
+        }
     }
-    if (chunk == chunks - 1 && threadIdx.x == 0) ptotal[0] = end;
+    if (group == L.groups - 1 && threadIdx.x == 0) ptotal[0] = base;
 }
 
 __device__ __forceinline__ bool key_better(float ka, int ia, float kb, int ib) {
@@ -240,14 +259,14 @@ __global__ __launch_bounds__(kBlock) void replay_threshold(const void* __restric
                                                            int K, float invT, const int32_t* __restrict__ topk_tok,
                                                            tsb_tree tree, uint32_t k0, uint32_t k1, uint32_t step,
                                                            int prune, int vec, float4* __restrict__ rec,
-                                                           int* __restrict__ plist, int* __restrict__ ptotal) {
-    const int chunks = (R * (B + 1) + kListNodes - 1) / kListNodes;
-    if ((int)blockIdx.x < chunks) {
-        prep_list(blockIdx.x, chunks, R, B, D, K, tree, plist, ptotal);
+                                                           int* __restrict__ plist, int* __restrict__ ptotal,
+                                                           ListSplit list) {
+    if ((int)blockIdx.x < list.groups) {
+        prep_list(blockIdx.x, list, R, B, D, K, tree, plist, ptotal);
         return;
     }
     const int lane = threadIdx.x % kWave;
-    const int node = ((int)blockIdx.x - chunks) * (kBlock / kWave) + threadIdx.x / kWave;
+    const int node = ((int)blockIdx.x - list.groups) * (kBlock / kWave) + threadIdx.x / kWave;
     if (node >= R * (B + 1)) return;
     const int r = node / (B + 1), u = node % (B + 1);
     TreeNode nd;
@@ -890,13 +909,14 @@ hipError_t launch_replay(const tsb_config& c, float invT, const void* draft, con
     float4* rec = (float4*)(ws + w.thr);
     // the parent list's workgroups, and one per four nodes
     const int nodes = c.R * (c.B + 1);
-    const int nthr = (nodes + kListNodes - 1) / kListNodes + (nodes + kBlock / kWave - 1) / (kBlock / kWave);
+    const ListSplit list = list_split(nodes);
+    const int nthr = list.groups + (nodes + kBlock / kWave - 1) / (kBlock / kWave);
     if (c.dtype == TSB_BF16)
         replay_threshold<TSB_BF16><<<nthr, kBlock, 0, st>>>(draft, c.R, c.V, c.D, c.B, c.K, invT, topk_tok, tree, k0,
-                                                            k1, step, prune, vec ? 1 : 0, rec, plist, ptotal);
+                                                            k1, step, prune, vec ? 1 : 0, rec, plist, ptotal, list);
     else
         replay_threshold<TSB_F32><<<nthr, kBlock, 0, st>>>(draft, c.R, c.V, c.D, c.B, c.K, invT, topk_tok, tree, k0,
-                                                           k1, step, prune, vec ? 1 : 0, rec, plist, ptotal);
+                                                           k1, step, prune, vec ? 1 : 0, rec, plist, ptotal, list);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int scan_id = tj ? TSB_KERNEL_SCAN_TARGET : TSB_KERNEL_REPLAY_SCAN;

@@ -112,3 +112,34 @@ def test_unpruned_rows_are_scored_whole(K, bad):
     parents = int((rnd.host()["n_children"] > 0).sum())
     assert s["replay_tokens"] == parents * V
     assert s["replay_groups_live"] == s["replay_groups_keyed"] == parents * V // 4
+
+
+@pytest.mark.parametrize("R,B", [(64, 1023), (65, 1023), (192, 700)])
+def test_parent_list_of_many_nodes(R, B):
+    """Batches whose parent list is one chunk of nodes to a workgroup (the most of them), and several: every parent
+    is listed once, and requests from both ends and the middle get the oracle's children."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    D, V, K, seed, step = 4, 64, 12, 6, 2
+    draft = (2.0 * torch.randn(R, D, V, generator=torch.Generator().manual_seed(R))).cuda()
+    rnd = tsb.Round(tsb.make_config(R, D, V, B, K, 1.0, "f32", seed), "cuda")
+    rnd.plan(draft)
+    tsb.stats_enable(True)
+    try:
+        tsb.stats_read()
+        rnd.replay(draft, step)
+        items = tsb.stats_read()["replay_items"]
+    finally:
+        tsb.stats_enable(False)
+    h = rnd.host()
+    assert items == int((h["n_children"] > 0).sum())
+    a = draft.cpu().double().numpy()
+    for r in (0, R // 3, R // 2, R - 1):
+        n = int(h["n_nodes"][r])
+        assert (h["node_tok"][r, 1:n] >= 0).all()
+        for u in range(n):
+            m, fc = int(h["n_children"][r, u]), int(h["first_child"][r, u])
+            if m == 0:
+                continue
+            toks, margin = oreplay.replay_node(a[r, int(h["depth"][r, u])], m, seed, step, r, u)
+            assert margin < 1e-5 or np.array_equal(h["node_tok"][r, fc:fc + m].numpy(), toks), (r, u, m)
