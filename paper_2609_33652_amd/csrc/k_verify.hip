@@ -694,17 +694,18 @@ struct FirstPass {
 
 // End of a walk: the request's outputs, and the optional normaliser output
 // (from the target stream's partials, which the caller streamed when it asked
-// for it). rows_bad < 0: every target row of the tree must be usable (from
-// the partials); otherwise rows_bad is the walk's own verdict on the rows it
-// entered.
-__device__ __forceinline__ void walk_tail(const WalkArgs& A, int r, int g, int G, int n, bool draft_bad, bool invalid, int nacc,
+// for it), both by the request's first workgroup: another one may start only
+// after this one has ended a walk without an exchange (an unusable root row),
+// and would take the status written here for the planner's. rows_bad < 0:
+// every target row of the tree must be usable (from the partials); otherwise
+// rows_bad is the walk's own verdict on the rows it entered.
+__device__ __forceinline__ void walk_tail(const WalkArgs& A, int r, int g, int n, bool draft_bad, bool invalid, int nacc,
                           int bonus_out, int add_status, int tcount, int rows_bad = -1) {
-    if (g != 0 && !A.out.target_lse) return;  // uniform over the workgroup
+    if (g != 0) return;  // uniform over the workgroup
     __shared__ int s_bad;
     const int tid = threadIdx.x;
     const int B1 = A.B + 1;
     const size_t tb = (size_t)r * B1;
-    const bool lead = (g == 0 && tid == 0);
     int* status_p = A.out.req_status + r;
     if (tid == 0) s_bad = 0;
     __syncthreads();
@@ -716,7 +717,7 @@ __device__ __forceinline__ void walk_tail(const WalkArgs& A, int r, int g, int G
     if (A.out.target_lse) {
         // a request rejected by a verifier that reads every row reports no normaliser
         const bool none = draft_bad || (bad && rows_bad < 0);
-        for (int i = g * kWalkThreads + tid; i < B1; i += G * kWalkThreads) {
+        for (int i = tid; i < B1; i += kWalkThreads) {
             double l = (double)NAN;
             if (!none && i < n) {
                 int b;
@@ -726,7 +727,7 @@ __device__ __forceinline__ void walk_tail(const WalkArgs& A, int r, int g, int G
             A.out.target_lse[tb + i] = l;
         }
     }
-    if (lead) {
+    if (tid == 0) {
         if (bad) {
             nacc = 0;
             bonus_out = -1;
@@ -991,7 +992,7 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4)
         }
     }
 
-    walk_tail(A, r, g, G, n, draft_bad, invalid, nacc, bonus_out, add_status, tcount, rows_bad);
+    walk_tail(A, r, g, n, draft_bad, invalid, nacc, bonus_out, add_status, tcount, rows_bad);
 }
 
 
@@ -1289,7 +1290,7 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4)
         __syncthreads();
         if (s_badtok) add_status |= TSB_REQ_BAD_TOKEN;
     }
-    walk_tail(A, r, g, G, n, draft_bad, invalid, nacc, bonus_out, add_status, tcount);
+    walk_tail(A, r, g, n, draft_bad, invalid, nacc, bonus_out, add_status, tcount);
 }
 
 // ---------------------------------------------------------- traversal walk
@@ -1600,7 +1601,7 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4)
         }
         if (X.timeout) add_status |= TSB_REQ_WALK_TIMEOUT;
     }
-    walk_tail(A, r, g, G, n, draft_bad, invalid, nacc, bonus_out, add_status, tcount);
+    walk_tail(A, r, g, n, draft_bad, invalid, nacc, bonus_out, add_status, tcount);
 }
 
 // ------------------------------------------------------------------ launch

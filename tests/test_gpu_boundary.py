@@ -204,3 +204,22 @@ def test_out_of_range_tokens_are_flagged():
     for r in (1, 2, 3):
         assert int(b["req_status"][r]) & tsb.REQ_BAD_TOKEN, r
         assert int(b["n_acc"][r]) == -1 and int(b["bonus"][r]) == -1
+
+
+@pytest.mark.parametrize("flags", [tsb.FLAG_STREAM_ROWS, tsb.FLAG_READ_ROWS])
+def test_normalisers_of_a_request_that_ends_at_its_root(flags):
+    """An unusable root row ends the RRS walk of a request before its workgroups have met: the normalisers of the
+    request's other rows, more than a workgroup has threads, are written all the same."""
+    R, V, D, B, K = 40, 4100, 5, 1000, 6
+    g = torch.Generator(device="cuda").manual_seed(3)
+    draft = torch.randn(R, D, V, generator=g, device="cuda").to(torch.bfloat16)
+    target = torch.randn(R, B + 1, V, generator=g, device="cuda").to(torch.bfloat16)
+    target[:, 0, V // 2] = float("nan")
+    rnd = tsb.Round(tsb.make_config(R, D, V, B, K, 1.0, "bf16", 4, flags), "cuda", target_lse=True)
+    for step in range(3):
+        rnd.step(draft, target, step)
+        lse = rnd.target_lse.clone()
+        assert (rnd.tree["n_nodes"] == B + 1).all()
+        assert (rnd.req_status & tsb.REQ_NONFINITE).all()
+        assert lse[:, 0].isnan().all()
+        assert lse[:, 1:].isfinite().all(), int(lse[:, 1:].isnan().sum())
