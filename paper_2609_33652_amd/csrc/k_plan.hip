@@ -342,6 +342,25 @@ __device__ __forceinline__ void tab_word(uint32_t w, const double* tab, double& 
     s1 += *(const double*)((const char*)tab + (off >> 16));
 }
 
+typedef short tsb_i16x2 __attribute__((ext_vector_type(2)));
+// Order-preserving signed 16-bit keys of the two bf16 patterns of a word
+// (a larger value has a larger key; -0 sits just below +0; NaN patterns sit
+// above +inf or below -inf by their sign).
+__device__ __forceinline__ tsb_i16x2 bf16_keys(uint32_t w) {
+    const tsb_i16x2 v = __builtin_bit_cast(tsb_i16x2, w);
+    const tsb_i16x2 sgn = v >> (tsb_i16x2){15, 15};  // 0 or -1 per half
+    return v ^ (sgn & (tsb_i16x2){0x7FFF, 0x7FFF});
+}
+
+// Key of the smallest bf16 value at least x (x not NaN): the pattern of a
+// positive x rounded up, of a negative x truncated toward zero.
+__device__ __forceinline__ int bf16_key_at_least(float x) {
+    const uint32_t b = __float_as_uint(x);
+    const uint32_t p = (b >> 31) ? (b >> 16) : ((b + 0xFFFFu) >> 16);
+    const int v = (int)(short)(uint16_t)p;
+    return v < 0 ? v ^ 0x7FFF : v;
+}
+
 // Whether some logit of the group (four words of bf16 pairs) has a key above
 // kf (k2 = kf in both halves).
 __device__ __forceinline__ bool group_reaches(const uint32_t (&w)[4], tsb_i16x2 k2) {

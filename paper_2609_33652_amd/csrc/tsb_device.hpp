@@ -159,26 +159,6 @@ __device__ __forceinline__ float load_logit(const void* base, size_t i) {
 }
 
 typedef unsigned short tsb_u16x2 __attribute__((ext_vector_type(2)));
-typedef short tsb_i16x2 __attribute__((ext_vector_type(2)));
-// Order-preserving signed 16-bit keys of the two bf16 patterns of a word
-// (a larger value has a larger key; -0 sits just below +0; NaN patterns sit
-// above +inf or below -inf by their sign).
-__device__ __forceinline__ tsb_i16x2 bf16_keys(uint32_t w) {
-    const tsb_i16x2 v = __builtin_bit_cast(tsb_i16x2, w);
-    const tsb_i16x2 sgn = v >> (tsb_i16x2){15, 15};  // 0 or -1 per half
-    return v ^ (sgn & (tsb_i16x2){0x7FFF, 0x7FFF});
-}
-
-// Key of the smallest bf16 value at least x (x not NaN): the pattern of a
-// positive x rounded up, of a negative x truncated toward zero.
-__device__ __forceinline__ int bf16_key_at_least(float x) {
-    const uint32_t b = __float_as_uint(x);
-    const uint32_t p = (b >> 31) ? (b >> 16) : ((b + 0xFFFFu) >> 16);
-    const int v = (int)(short)(uint16_t)p;
-    return v < 0 ? v ^ 0x7FFF : v;
-}
-
-constexpr int kBf16KeyMinusInf = -0x7F81;  // key of pattern 0xFF80
 
 // 16-byte load with the non-temporal hint, for data read exactly once.
 typedef unsigned int tsb_u32x4 __attribute__((ext_vector_type(4)));
@@ -300,26 +280,14 @@ __device__ __forceinline__ int wave_or(int v) {
     for (int o = 32; o > 0; o >>= 1) v |= (int)xor_lane_red_u32((uint32_t)v, o);
     return v;
 }
-// Whole-wave one-lane shifts through DPP (lane i receives lane i-1, resp.
-// i+1; the edge lane keeps its own value) and reads of one lane's value
-// (the lane index must be wave-uniform).
+// Whole-wave one-lane shift through DPP (lane i receives lane i-1; lane 0
+// keeps its own value) and reads of one lane's value (the lane index must be
+// wave-uniform).
 __device__ __forceinline__ uint32_t wave_shr1(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x138, 0xf, 0xf, false);
 }
-__device__ __forceinline__ uint32_t wave_shl1(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x130, 0xf, 0xf, false);
-}
 __device__ __forceinline__ uint64_t wave_shr1(uint64_t v) {
     return ((uint64_t)wave_shr1((uint32_t)(v >> 32)) << 32) | wave_shr1((uint32_t)v);
-}
-__device__ __forceinline__ uint64_t wave_shl1(uint64_t v) {
-    return ((uint64_t)wave_shl1((uint32_t)(v >> 32)) << 32) | wave_shl1((uint32_t)v);
-}
-__device__ __forceinline__ double wave_shr1(double v) {
-    return __longlong_as_double((long long)wave_shr1((uint64_t)__double_as_longlong(v)));
-}
-__device__ __forceinline__ double wave_shl1(double v) {
-    return __longlong_as_double((long long)wave_shl1((uint64_t)__double_as_longlong(v)));
 }
 __device__ __forceinline__ uint32_t lane_u32(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
 __device__ __forceinline__ float lane_f32(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
@@ -460,27 +428,6 @@ struct WaveTopList {
             thr = lane_u64(v, k - 1);
         }
     }
-    // As offer, for candidates given as (logit, id): the key is formed only
-    // for the one candidate being inserted (from wave-uniform values).
-    __device__ void offer_xid(float x, uint32_t id, bool want) {
-        uint64_t ballot = __ballot(want);
-        const int lane = lane_id();
-        while (ballot) {
-            const int src = __ffsll((unsigned long long)ballot) - 1;
-            ballot &= ballot - 1;
-            const uint64_t c = cand_key(lane_f32(x, src), lane_u32(id, src));
-            if (c <= thr) continue;
-            const int pos = __popcll(__ballot(lane < k && v > c));
-            const uint64_t up = wave_shr1(v);
-            if (lane < k) {
-                if (lane == pos)
-                    v = c;
-                else if (lane > pos)
-                    v = up;
-            }
-            thr = lane_u64(v, k - 1);
-        }
-    }
 };
 
 // Orders a wave's LDS accesses before and after this point (for lanes that
@@ -534,23 +481,6 @@ __device__ __forceinline__ void wave_sort_desc(uint64_t (&v)[NR]) {
 // Number of lanes below this one whose bit is set in b.
 __device__ __forceinline__ int lanes_below_u64(uint64_t b) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
-}
-
-// Exclusive prefix sum over the lanes of small non-negative counts
-// (< 2^NB), one ballot per bit; `total` receives the wave sum.
-template <int NB>
-__device__ __forceinline__ int wave_excl_scan(int c, int& total) {
-    int off = 0;
-    total = 0;
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const uint64_t m = __ballot((c >> b) & 1);
-        const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        off += below << b;
-        total += __popcll(m) << b;
-    }
-    return off;
 }
 
 // The k-th largest (1 <= k <= 64) of the values held by the 64 lanes, NaN

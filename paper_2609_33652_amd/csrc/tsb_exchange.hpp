@@ -3,10 +3,11 @@
 //
 // Layout (a workspace region): slots [R][2][kWalkGroupsMax][kSlotWords]
 // 64-bit words; round e of request r uses the slot pair of parity e & 1. A
-// publisher (thread 0 of a workgroup, or a lane of its wave 0 per word) writes
-// each word with one relaxed agent-scope store; every word carries the round's 8-bit tag in its low
-// bits, so a reader knows it holds all words of the current round without
-// any ordering between the stores:
+// publisher writes each word with one relaxed agent-scope store (all eight by
+// thread 0 in the Naive walk, the four in use by a lane of wave 0 each in the
+// other walks); every word carries the round's 8-bit tag in its low bits, so a
+// reader knows it holds all words of the current round without any ordering
+// between the stores:
 //   tag(e) = (e & 1) << 7 | ((e >> 1) % 127 + 1)
 // never 0, and different for rounds e and e - 2, the only earlier round a
 // slot can still hold (a workgroup publishes round e only after reading
@@ -66,17 +67,14 @@ __device__ __forceinline__ int xticket(const XRegion& X, int R) {
 }
 
 // Zeroes the exchange slots of R requests and the ticket counter; thread `i`
-// of `n` threads
-// (grid-stride) takes every n-th word.
+// of `n` threads (grid-stride) takes every n-th word.
 __device__ __forceinline__ void xclear(const XRegion& X, int R, size_t i, size_t n) {
     const size_t nw = xwords(R);
     for (; i < nw; i += n) __hip_atomic_store(&X.slots[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Payload packing: a binary64 value keeps all but its 8 lowest mantissa bits
+// Payloads: a binary64 value keeps all but its 8 lowest mantissa bits
 // (relative resolution 2^-44); 32-bit payloads sit in the high half.
-__device__ __forceinline__ uint64_t xpack_f64(double x) { return (uint64_t)__double_as_longlong(x) & ~kTagMask; }
-__device__ __forceinline__ double xunpack_f64(uint64_t w) { return __longlong_as_double((long long)(w & ~kTagMask)); }
 __device__ __forceinline__ uint64_t xpack_u32(uint32_t x) { return (uint64_t)x << 32; }
 __device__ __forceinline__ uint32_t xunpack_u32(uint64_t w) { return (uint32_t)(w >> 32); }
 
