@@ -1,10 +1,10 @@
 """The walks where a request's vocabulary slices change shape: one workgroup
-(no exchange) and the first two-workgroup vocabulary, slices of one, two and
-three groups a thread, a last slice that is short or empty, odd vocabularies
-(no vector loads), slices that leave a compute unit to one workgroup, and
-vocabularies whose slices are recomputed in every pass. Small and equal draft
-and target rows make some walks accept and others reject every child, so both
-bonus draws and the residual passes run.
+(no exchange) and the first vocabulary of several, slices of one, two, three
+and five groups a thread, a last slice that is short, odd vocabularies (no
+vector loads), slices that leave a compute unit to one workgroup, the longest
+held ones, and vocabularies whose slices are recomputed in every pass. Small
+and equal draft and target rows make some walks accept and others reject every
+child, so both bonus draws and the residual passes run.
 
 A whole round and the staged calls must agree bit for bit, and both with the
 oracle's round: path, bonus and status, unless one of its decisions has a
@@ -20,7 +20,7 @@ from oracle import step as ostep
 pytestmark = pytest.mark.gpu
 
 SMALL = [(5, 2), (1024, 2), (4096, 2), (4097, 2), (8188, 3), (9601, 2), (32000, 2), (65537, 2), (131070, 1)]
-WIDE = [(524288, 1), (614403, 1), (1212420, 1), (1212416 + 4096, 1)]
+WIDE = [(524288, 1), (614403, 1), (1212416, 1), (1212420, 1), (1212416 + 4096, 1)]
 
 
 def _round(V, R, dtype, verifier, flags, mix):
