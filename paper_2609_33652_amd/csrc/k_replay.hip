@@ -205,9 +205,17 @@ __device__ __forceinline__ void load_group4(const void* __restrict__ draft, size
 // from (the first 1024 or 2048 tokens of the row; twice as many cost the
 // threshold what they save the scan). Sampled are rows of at least
 // kSampleMinV tokens (a row of a few tiles has few keys above any threshold)
-// in calls of at least kSampleMinNodes nodes: 65 nodes are scanned in the
-// same 12.7 us either way, and the sample takes 3 us; 520 nodes (8 x 65 x
-// 151936) go from 35.4 to 22.3 us.
+// in calls of at least kSampleMinNodes nodes.
+//
+// What decides is the rows' spread, more than the nodes. A replay without and
+// with the sample, 151936 logits, at 65, 256 and 520 nodes (us): standard
+// deviation 0.05 37.6 / 25.7, 40.0 / 28.4, 48.4 / 32.0; 1: 33 / 29, 36 / 31,
+// 42 / 34; rows of 1 to 6: 29.5 / 27.6, 31.2 / 30.5, 38.3 / 35.2; of 2 to 5:
+// 25.2 / 25.8, 27.4 / 29.3, 31.6 / 34.2; 6: 17.9 / 20.7, 20.3 / 23.3, 32.3 /
+// 35.4 (32000 logits: the same to 2 us). So it costs steep rows 1 to 3 us at
+// any size and saves flat ones 4 to 16. The rule does not know the spread:
+// below the line, calls of few requests, whose rows are mostly steep, go
+// without it; above, batches mix rows and the flattest end the scan.
 constexpr int kSampleGroups = 4;
 constexpr int kSampleFewChildren = 4;  // up to this many children one round of groups, else two
 constexpr int kSampleMinV = 4 * kReplayTile;

@@ -2,10 +2,11 @@
 // Appendix A: recursive rejection sampling without replacement; Section 3.3:
 // the probabilities are those of the replayed candidates).
 //
-//   target_partials  grid (segment, request x node): one streaming read of
-//                    every target row of the tree; online max and sum of
-//                    exp per segment (binary32 terms, binary64 per lane).
-//   verify_walk      resident grid (G workgroups per request). All G
+//   target_partials  a workgroup per chunk of the flat target: one streaming
+//                    read of every target row of the tree; online max and sum
+//                    of exp per piece of a row (binary32 terms, binary64 per
+//                    lane). More workgroups write the walk's node records.
+//   verify_walk      G workgroups per request, by tickets. All G
 //                    workgroups of a request replay the same scalar walk;
 //                    every vocabulary-wide reduction of the walk (residual
 //                    mass after a rejection, the bonus draw) is split over
@@ -115,8 +116,18 @@ __device__ __forceinline__ SplitF split(double v) {
 // recomputed in every pass.
 //
 // Bound by latency: a node is a chain of its record's load, its rows' load
-// and an exchange. Slices were 9728 tokens, one workgroup of 512 threads on a
-// compute unit with 19 tokens a thread to evaluate and to read in every pass.
+// (after the record: the topology checks come first) and an exchange. Slices
+// were 9728 tokens, one workgroup of 512 threads on a compute unit with 19
+// tokens a thread to evaluate and to read in every pass.
+//
+// Registers: the three walks are held to 128, so that two workgroups of eight
+// waves share a compute unit; what does not fit goes to scratch (verify_walk 60
+// bytes a lane for bf16, 44 for binary32, verify_pool_walk 12 to 20,
+// verify_traversal none for bf16, 64 for binary32). Left to the compiler they
+// take 160, 140 and 154, one workgroup a compute unit: 16 requests of 151936
+// tokens 78 -> 90 to 102 us and 64 requests 254 to 290 -> 344 to 395, the pool
+// walk 58 -> 88; one request alone, all of whose workgroups run at once
+// either way, 29.1 -> 27.5.
 constexpr int kWalkThreads = kWalkThreadsPerGroup;
 constexpr int kWalkWaves = kWalkThreads / kWave;
 constexpr int kWalkPass = 4 * kWalkThreads;  // tokens of one group per thread
@@ -846,8 +857,8 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4)
             }
             const int m = N.t.m, fc = N.t.fc;
             const size_t drow = ((size_t)r * A.D + (m > 0 ? N.t.d : 0)) * (size_t)A.V;
-            // the rows' slices are in flight while the normaliser and the first
-            // test are worked out
+            // the rows' slices are in flight while the children's probabilities
+            // and, where it is known, the normaliser are worked out
             rt.load(A.target, vec, S, trow);
             if (m > 0) rd.load(A.draft, vec, S, drow);
             // the streamed normaliser of u's row, and whether the row is usable
@@ -1680,8 +1691,8 @@ static hipError_t launch_target_partials(const tsb_config& c, float invT, const 
 
 // Rows 0 and 1 of every request for a walk that reads the other rows itself
 // (tsb_verify; a round streams them beside the planner), the clearing of the
-// walk's exchange slots and, on the workgroups after those, its node records. No profiling id: tsb_profile_kernel's target
-// stream is target_partials alone.
+// walk's exchange slots and, on the workgroups after those, its node records.
+// No profiling id: tsb_profile_kernel's target stream is target_partials alone.
 template <int DT, bool VEC>
 __global__ __launch_bounds__(kChainThreads) void chain_rows(ChainJob cj, XRegion X, int R, float invT, int nchain,
                                                             RecordJob rec) {

@@ -22,7 +22,8 @@ constexpr int kWalkGroupsMax = 128;  // workgroups per request in verification
 constexpr int kWalkThreadsPerGroup = 512;
 // Tokens whose binary64 (p, q) a walk workgroup holds in LDS: up to
 // kWalkSliceTokens with another workgroup beside it on the compute unit (77 KB
-// of its 160 each), kWalkHeldTokens at most.
+// of its 160 each), kWalkHeldTokens at most (a device with fewer compute units
+// than a request's workgroups runs fewer of them, with longer slices).
 constexpr int kWalkSliceTokens = 4800, kWalkHeldTokens = 9472;
 constexpr int kWalkResident = 512;      // walk workgroups two to a compute unit
 constexpr int kTargetWorkgroups = 2048;  // target stream: 8 resident workgroups on each of 256 CUs

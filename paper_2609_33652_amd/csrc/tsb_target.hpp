@@ -26,13 +26,14 @@ constexpr bool kTargetPrefetch = true;
 // of the caches' normal allocation was measured ~11% faster on this part.
 //
 // Layout: the target is one flat array of R (B+1) V logits cut into equal
-// chunks (at least kTargetMinChunk logits, at most kTargetWorkgroups of
-// them). The target kernel's own grid has one workgroup per chunk, all
-// resident at once, so none trails the others; the replay scan's grid deals
-// the chunks over fewer workgroups. A chunk covers pieces of one or more
-// rows; the k-th chunk that meets row t gives partial slot k of the row, and
-// the chunk holding the row's first logit marks the slots no piece uses as
-// empty, so the partials depend on the chunking only, never on the grid.
+// chunks (of at least kTargetMinChunk logits, or of one row where rows are
+// shorter, and at most kTargetWorkgroups of them). The target kernel's own
+// grid has one workgroup per chunk, all resident at once, so none trails the
+// others; the replay scan's grid deals the chunks over fewer workgroups. A
+// chunk covers pieces of one or more rows; the k-th chunk that meets row t
+// gives partial slot k of the row, and the chunk holding the row's first logit
+// marks the slots no piece uses as empty, so the partials depend on the
+// chunking only, never on the grid.
 // The chunks also zero the exchange slots of the walk launched after them.
 template <int DT, bool VEC, bool PREF, int NT = kBlock>
 __device__ __forceinline__ void stream_piece(const void* __restrict__ target, size_t rowbase, int lo, int hi,
