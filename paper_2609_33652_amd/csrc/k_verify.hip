@@ -121,13 +121,13 @@ __device__ __forceinline__ SplitF split(double v) {
 // tokens a thread to evaluate and to read in every pass.
 //
 // Registers: the three walks are held to 128, so that two workgroups of eight
-// waves share a compute unit; what does not fit goes to scratch (verify_walk 60
-// bytes a lane for bf16, 44 for binary32, verify_pool_walk 12 to 20,
-// verify_traversal none for bf16, 64 for binary32). Left to the compiler they
-// take 160, 140 and 154, one workgroup a compute unit: 16 requests of 151936
-// tokens 78 -> 90 to 102 us and 64 requests 254 to 290 -> 344 to 395, the pool
-// walk 58 -> 88; one request alone, all of whose workgroups run at once
-// either way, 29.1 -> 27.5.
+// waves share a compute unit; what does not fit goes to scratch (verify_walk 56
+// bytes a lane for bf16, 40 to 44 for binary32; verify_pool_walk 12 to 20;
+// verify_traversal none for bf16, 60 to 64 for binary32). Left to the compiler
+// they take 160 to 168, 140, and 127 and 154, mostly one workgroup a compute
+// unit: verify_walk over 16 requests of 151936 tokens 78 -> 90 to 102 us (three
+// inputs), over 64 254 to 290 -> 344 to 395, the pool walk over 16 58 -> 88; one
+// request alone, whose workgroups all run at once either way, 29.1 -> 27.5.
 constexpr int kWalkThreads = kWalkThreadsPerGroup;
 constexpr int kWalkWaves = kWalkThreads / kWave;
 constexpr int kWalkPass = 4 * kWalkThreads;  // tokens of one group per thread
@@ -707,12 +707,14 @@ struct FirstPass {
 // (from the target stream's partials, which the caller streamed when it asked
 // for it), both by the request's first workgroup: another one may start only
 // after this one has ended a walk without an exchange (an unusable root row),
-// and would take the status written here for the planner's. rows_bad < 0:
-// every target row of the tree must be usable (from the partials); otherwise
-// rows_bad is the walk's own verdict on the rows it entered.
+// and would take the status written here for the planner's. (A return of
+// every other workgroup at once costs verify_walk a register more of scratch,
+// 0.2 us of 18.4.) rows_bad < 0: every target row of the tree must be usable
+// (from the partials); otherwise rows_bad is the walk's own verdict on the rows
+// it entered.
 __device__ __forceinline__ void walk_tail(const WalkArgs& A, int r, int g, int n, bool draft_bad, bool invalid, int nacc,
                           int bonus_out, int add_status, int tcount, int rows_bad = -1) {
-    if (g != 0) return;  // uniform over the workgroup
+    if (g != 0 && !A.out.target_lse) return;  // uniform over the workgroup
     __shared__ int s_bad;
     const int tid = threadIdx.x;
     const int B1 = A.B + 1;
@@ -728,7 +730,7 @@ __device__ __forceinline__ void walk_tail(const WalkArgs& A, int r, int g, int n
     if (A.out.target_lse) {
         // a request rejected by a verifier that reads every row reports no normaliser
         const bool none = draft_bad || (bad && rows_bad < 0);
-        for (int i = tid; i < B1; i += kWalkThreads) {
+        for (int i = tid; g == 0 && i < B1; i += kWalkThreads) {
             double l = (double)NAN;
             if (!none && i < n) {
                 int b;
@@ -738,7 +740,7 @@ __device__ __forceinline__ void walk_tail(const WalkArgs& A, int r, int g, int n
             A.out.target_lse[tb + i] = l;
         }
     }
-    if (tid == 0) {
+    if (g == 0 && tid == 0) {
         if (bad) {
             nacc = 0;
             bonus_out = -1;
