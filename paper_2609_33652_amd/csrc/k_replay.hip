@@ -811,12 +811,10 @@ __global__ __launch_bounds__(kWave) void replay_merge(int B, int D, int K, int T
     // 64 tiles at a time, lane t holds tile t's count; the keys of their slots
     // (in no order) are gathered contiguously, their indices placed through LDS
     // (reading every slot of 65 tiles took 21.5 us for one request of 65 nodes
-    // and 29.3 for 16 of 129, gathering them 12.0 and 18.6)
+    // and 29.3 for 16 of 129, gathering them 11.6 and 17.9)
     __shared__ uint16_t s_idx[kWave * TSB_MAX_K];
     __shared__ uint64_t s_key[kWave];
-    WaveTopList top;
-    top.init(m);
-    for (int t0 = 0; t0 < T; t0 += kWave) {
+    auto gather = [&](int t0) -> int {
         const int ct = t0 + lane < T ? cc[o + t0 + lane] : 0;
         int nv = 0;
         for (int j = 0;; ++j) {
@@ -826,57 +824,63 @@ __global__ __launch_bounds__(kWave) void replay_merge(int B, int D, int K, int T
             nv += __popcll(bj);
         }
         wave_lds_fence();
-        const uint64_t* cb = cand + (o + t0) * TSB_MAX_K;
-        // the keys are loaded together, up to kMergeKeys a lane. The m-th
-        // largest of the lane maxima is a lower bound of the m-th key (lanes hold
-        // distinct keys): the few keys that reach it are compacted, one per lane,
-        // and a key's rank is the number of larger ones. (A sort of 64 keys takes
-        // about 1.3 us here, an insert 0.15 us.)
-        constexpr int kMergeKeys = 12;
-        if (T <= kWave && nv <= kMergeKeys * kWave) {
-            uint64_t kb[kMergeKeys], mx = 0ull;
+        return nv;
+    };
+    int nv = gather(0);
+    const uint64_t* cb = cand + o * TSB_MAX_K;
+    // the keys are loaded together, up to kMergeKeys a lane. The m-th
+    // largest of the lane maxima is a lower bound of the m-th key (lanes hold
+    // distinct keys): the few keys that reach it are compacted, one per lane,
+    // and a key's rank is the number of larger ones. (A sort of 64 keys takes
+    // about 1.3 us here, an insert 0.15 us.)
+    constexpr int kMergeKeys = 12;
+    if (T <= kWave && nv <= kMergeKeys * kWave) {
+        uint64_t kb[kMergeKeys], mx = 0ull;
+#pragma unroll
+        for (int q = 0; q < kMergeKeys; ++q) {
+            const int e = q * kWave + lane;
+            kb[q] = e < nv ? cb[s_idx[e]] : 0ull;
+        }
+        int c = nv;
+        uint64_t mine = kb[0];
+        if (nv > kWave) {
+#pragma unroll
+            for (int q = 0; q < kMergeKeys; ++q) mx = kb[q] > mx ? kb[q] : mx;
+            const uint32_t hi = (uint32_t)(mx >> 32);
+            int above = 0;
+            for (int l = 0; l < kWave; ++l) above += lane_u32(hi, l) > hi ? 1 : 0;
+            // the smallest of the maxima with fewer than m above them
+            uint32_t lo = above < m ? hi : 0xFFFFFFFFu;
+#pragma unroll
+            for (int f = 32; f > 0; f >>= 1) lo = min(lo, xor_lane_red_u32(lo, f));
+            c = 0;
 #pragma unroll
             for (int q = 0; q < kMergeKeys; ++q) {
-                const int e = q * kWave + lane;
-                kb[q] = e < nv ? cb[s_idx[e]] : 0ull;
+                const bool keep = (uint32_t)(kb[q] >> 32) >= lo;
+                const uint64_t b = __ballot(keep);
+                const int at = c + lanes_below_u64(b);
+                if (keep && at < kWave) s_key[at] = kb[q];
+                c += __popcll(b);
             }
-            int c = nv;
-            uint64_t mine = kb[0];
-            if (nv > kWave) {
-#pragma unroll
-                for (int q = 0; q < kMergeKeys; ++q) mx = kb[q] > mx ? kb[q] : mx;
-                const uint32_t hi = (uint32_t)(mx >> 32);
-                int above = 0;
-                for (int l = 0; l < kWave; ++l) above += lane_u32(hi, l) > hi ? 1 : 0;
-                // the smallest of the maxima with fewer than m above them
-                uint32_t lo = above < m ? hi : 0xFFFFFFFFu;
-#pragma unroll
-                for (int f = 32; f > 0; f >>= 1) lo = min(lo, xor_lane_red_u32(lo, f));
-                c = 0;
-#pragma unroll
-                for (int q = 0; q < kMergeKeys; ++q) {
-                    const bool keep = (uint32_t)(kb[q] >> 32) >= lo;
-                    const uint64_t b = __ballot(keep);
-                    const int at = c + lanes_below_u64(b);
-                    if (keep && at < kWave) s_key[at] = kb[q];
-                    c += __popcll(b);
-                }
-                wave_lds_fence();
-                mine = lane < c ? s_key[lane] : 0ull;
-                wave_lds_fence();
-            }
-            if (c <= kWave) {
-                int rank = 0;
-                for (int l = 0; l < c; ++l) rank += lane_u64(mine, l) > mine ? 1 : 0;
-                if (lane < c) s_key[rank] = mine;
-                wave_lds_fence();
-                finish((int32_t)cand_id(lane < c ? s_key[lane] : 0ull));
-                return;
-            }
+            wave_lds_fence();
+            mine = lane < c ? s_key[lane] : 0ull;
+            wave_lds_fence();
         }
-        // more keys than that, ties of their upper halves, or more tiles:
-        // inserted in batches of 64, the loads of several in flight together
-        constexpr int kMergeBatches = 8;
+        if (c <= kWave) {
+            int rank = 0;
+            for (int l = 0; l < c; ++l) rank += lane_u64(mine, l) > mine ? 1 : 0;
+            if (lane < c) s_key[rank] = mine;
+            wave_lds_fence();
+            finish((int32_t)cand_id(lane < c ? s_key[lane] : 0ull));
+            return;
+        }
+    }
+    // more keys than that, ties of their upper halves, or more tiles: inserted
+    // in batches of 64, the loads of several in flight together
+    WaveTopList top;
+    top.init(m);
+    constexpr int kMergeBatches = 8;
+    for (int t0 = 0;;) {
         for (int b0 = 0; b0 < nv; b0 += kMergeBatches * kWave) {
             uint64_t kb[kMergeBatches];
 #pragma unroll
@@ -887,7 +891,11 @@ __global__ __launch_bounds__(kWave) void replay_merge(int B, int D, int K, int T
 #pragma unroll
             for (int q = 0; q < kMergeBatches; ++q) top.offer(kb[q], kb[q] != 0);
         }
+        t0 += kWave;
+        if (t0 >= T) break;
         wave_lds_fence();  // the next tiles' indices take their place
+        nv = gather(t0);
+        cb += kWave * TSB_MAX_K;
     }
     finish((int32_t)cand_id(top.v));
 }
