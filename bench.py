@@ -41,10 +41,10 @@ POOL_KERNELS = ("pool_partials", "pool_lists", "pool_plan", "pool_replay", "targ
 COUNTERS = {
     # the round's launch at the batched workload, where the walk reads the
     # target rows of the nodes it enters (the grid scans and clears only)
-    "scan_target": {"config": 4, "source_sha256_16": "3be3d5f45dcaad1e", "fetch_kib": 41075.6, "write_kib": 988.9,
-                    "insts_valu": 22214759.5},
-    "target_partials": {"config": 4, "source_sha256_16": "e7687f67d6cf1f49", "fetch_kib": 312009.3,
-                        "write_kib": 518.2, "insts_valu": 35369697.0},
+    "scan_target": {"config": 4, "source_sha256_16": "56b3d7ffcecbd351", "fetch_kib": 41064.9, "write_kib": 988.9,
+                    "insts_valu": 22215296.9},
+    "target_partials": {"config": 4, "source_sha256_16": "731ee7ea315e2a4e", "fetch_kib": 312212.6,
+                        "write_kib": 519.3, "insts_valu": 35369697.0},
 }
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 # peak VALU issue: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3e12 lane
