@@ -263,8 +263,10 @@ tsb_status tsb_step_noalloc(const tsb_config* cfg, const void* draft, const void
  * node (BONUS stream of that node); U of a tested node comes from its
  * ACCEPT stream. An empty residual (T <= 0 with alpha_u = 1, or an
  * exhausted Ms_u with children left) ends the round at u with a bonus from
- * p_u and TSB_REQ_DEGENERATE_RESIDUAL. trace rows are (tested node, U,
- * alpha, T after its rejection or -1). */
+ * p_u and TSB_REQ_DEGENERATE_RESIDUAL. A topology in which nodes share
+ * children (not a tree, though every node is well formed) is flagged with
+ * TSB_REQ_BAD_TREE once as many tests have failed as it has nodes. trace rows
+ * are (tested node, U, alpha, T after its rejection or -1). */
 tsb_status tsb_verify_traversal(const tsb_config* cfg, const void* draft, const double* draft_lse,
                                 const void* target, const tsb_tree* tree, const int32_t* node_tok, uint32_t step,
                                 const tsb_verdict* out, void* workspace, size_t workspace_bytes,

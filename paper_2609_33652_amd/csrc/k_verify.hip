@@ -1434,8 +1434,10 @@ __global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4)
         int end_kind = 0;
         int leaf = -1;  // an accepted leaf child of E.node
         while (true) {
-            // every workgroup reads the same entries, so all take the same exits
-            if (!N.t.ok) {
+            // every workgroup reads the same entries, so all take the same exits;
+            // a tree's nodes are tested once each, nodes that share children would
+            // be once per path, of which there can be m^depth
+            if (!N.t.ok || tcount >= n) {
                 add_status |= TSB_REQ_BAD_TREE;
                 invalid = true;
                 break;

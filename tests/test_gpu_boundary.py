@@ -223,3 +223,39 @@ def test_normalisers_of_a_request_that_ends_at_its_root(flags):
         assert (rnd.req_status & tsb.REQ_NONFINITE).all()
         assert lse[:, 0].isnan().all()
         assert lse[:, 1:].isfinite().all(), int(lse[:, 1:].isnan().sum())
+
+
+def test_traversal_of_shared_children_ends():
+    """Layers of four nodes that all name the next layer as their children: 4^15 paths, each of which a traversal
+    that rejects everything would take. The request is flagged; the other one's round is untouched."""
+    V, D, W, L = 64, 16, 4, 15
+    B = W * L
+    g = torch.Generator(device="cuda").manual_seed(5)
+    draft = 0.1 * torch.randn(2, D, V, generator=g, device="cuda")
+    target = 0.1 * torch.randn(2, B + 1, V, generator=g, device="cuda")
+    target[1, :, :W] -= 60.0  # tokens 0 to 3 are never accepted
+    c = tsb.make_config(2, D, V, B, 4, 1.0, "f32", 9)
+    ref, dag = tsb.Round(c, "cuda"), tsb.Round(c, "cuda")
+    ref.plan(draft)
+    ref.replay(draft, 1)
+    t = {k: v.clone() for k, v in ref.tree.items()}
+    tok = ref.node_tok.clone()
+    u = torch.arange(1, B + 1, device="cuda", dtype=torch.int32)
+    layer = (u - 1) // W + 1
+    t["n_nodes"][1] = B + 1
+    t["depth"][1, 1:], t["rank"][1, 1:], t["parent"][1, 1:] = layer, (u - 1) % W, 0
+    t["n_children"][1, 0], t["first_child"][1, 0] = W, 1
+    t["n_children"][1, 1:] = torch.where(layer < L, W, 0).int()
+    t["first_child"][1, 1:] = torch.where(layer < L, layer * W + 1, -1).int()
+    tok[1, 1:] = (u - 1) % W
+    dag.load_tree(t)
+    dag.node_tok.copy_(tok)
+    dag.draft_lse.copy_(ref.draft_lse)
+    for rnd in (ref, dag):
+        rnd.req_status.zero_()
+        rnd.verify_traversal(draft, target, 1)
+    a, b = ref.host(), dag.host()
+    for k in ("n_acc", "acc_node", "acc_tok", "bonus", "req_status"):
+        assert torch.equal(a[k][0], b[k][0]), k
+    assert int(b["req_status"][1]) == tsb.REQ_BAD_TREE
+    assert int(b["n_acc"][1]) == -1 and int(b["bonus"][1]) == -1
